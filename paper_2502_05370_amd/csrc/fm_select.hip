@@ -1,15 +1,22 @@
 // Similarity-aware prefetch-set selection (Section 4.3, Eq. 6-8).
 //
-// One wavefront per (query, layer) row; lane j holds expert j (E <= 64).
+// One lane per expert; a wavefront holds 64 / SW rows of (query, layer), SW
+// the power of two from 8 to 64 that holds the E experts (8 rows for E = 8,
+// one for E = 60: a row of its own per wavefront left 56 of 64 lanes idle at
+// E = 8).
 //   1. Guiding probabilities: the matched map's row (float64 widening of the
 //      stored value), or the similarity-weighted mean of the kept matches'
 //      rows, summed in match order with explicit float64 roundings.
 //   2. Threshold: fixed tau, or delta = Clip(1 - score, 0, 1).
-//   3. Rank of lane j = experts ahead of it in (probability descending,
-//      index ascending) order; NaN probabilities rank last.
+//   3. Rank of an expert = experts ahead of it in (probability descending,
+//      index ascending) order; NaN probabilities rank last.  The rank is
+//      counted against the row's keys read from LDS, two instructions per
+//      key (rank_row below): the kernel is bound by vector instructions.
 //   4. The running sum over that order is taken sequentially in float64; k*
 //      is the first prefix reaching the threshold (E if none), clamped to
-//      [k_min, k_max]; the mask is the ballot of lanes with rank < k.
+//      [k_min, k_max]; the mask is the ballot of lanes with rank < k.  Past
+//      k_max entries the sum cannot change the clamped size, so it stops
+//      there.
 #include "fm_device.h"
 #include "fm_guide.h"
 #include "fm_internal.h"
@@ -36,134 +43,212 @@ struct SelArgs {
   uint32_t* flags;
 };
 
-// (p_i, i) is ahead of (p_j, j): larger probability, or equal and lower index;
-// NaN is behind every number and NaNs keep index order.
-__device__ __forceinline__ bool ahead(double pi, int i, double pj, int j) {
-  const bool ni = pi != pi, nj = pj != pj;
-  if (ni || nj) return (!ni && nj) || (ni && nj && i < j);
-  return pi > pj || (pi == pj && i < j);
-}
-
 }  // namespace
 
-// Ordered 64-bit key of a float64 probability: larger value -> larger key,
-// -0 and +0 equal, NaN lowest (key 0).  Ranking by (key desc, index asc) is
-// the (p desc, j asc, NaN last) order of ahead().
+// Ordered keys of a probability: larger value -> larger key, -0 and +0
+// equal, NaN lowest.  Ranking by (key desc, index asc) is the (p desc, j asc,
+// NaN last) order.  Real keys are at least 1; 0 marks a lane without an
+// expert.
 __device__ __forceinline__ uint64_t ord_f64(double p) {
-  if (p != p) return 0ull;
+  if (p != p) return 1ull;
   const uint64_t u = static_cast<uint64_t>(__double_as_longlong(p + 0.0));
   return (u >> 63) ? ~u : (u | 0x8000000000000000ull);
 }
+__device__ __forceinline__ uint32_t ord_f32(float p) {
+  if (p != p) return 1u;
+  const uint32_t u = __float_as_uint(p + 0.0f);
+  return (u >> 31) ? ~u : (u | 0x80000000u);
+}
 
-// The selection of row (b, l) of the batch from the query's matches idx_b /
-// score_b (k of them, best first) and its layer bounds lb[b] / le[b] (as
-// given; clamped here); one wavefront, lane j = expert j.
-__device__ __forceinline__ void select_row(const SelArgs& a, int b, int l, int lo, int hi, const int32_t* idx_b,
-                                           const float* score_b, double* sorted, uint64_t* keys) {
+// Rank of this lane's key among the E keys of its row (SW consecutive lanes):
+// the keys ahead of it, that is greater, or equal with a lower index.  The
+// borrow of mine - key_i - c, with c = 1 in the lanes after i, is exactly
+// "key_i is ahead of mine": one subtraction chain and one add-with-carry per
+// key, no separate test for equal keys.  `row` is the row's keys in LDS.
+// (gfx950: the carry mask of the subtraction is any scalar pair.)
+template <int SW>
+__device__ __forceinline__ int rank_row(const uint32_t* row, uint32_t mine, int E) {
+  // lanes whose index in the row is above i
+  uint64_t after = ~0ull;
+  if constexpr (SW == 8) after = 0xFEFEFEFEFEFEFEFEull;
+  else if constexpr (SW == 16) after = 0xFFFEFFFEFFFEFFFEull;
+  else if constexpr (SW == 32) after = 0xFFFFFFFEFFFFFFFEull;
+  else after = 0xFFFFFFFFFFFFFFFEull;
+  uint32_t rank = 0;
+  for (int i = 0; i < E; i += 4) {
+    const uint32x4 k = *reinterpret_cast<const uint32x4*>(row + i);
+#pragma unroll
+    for (int u = 0; u < 4; ++u) {
+      uint32_t t;
+      asm("v_subb_co_u32_e64 %0, vcc, %2, %3, %4\n\tv_addc_co_u32_e32 %1, vcc, 0, %1, vcc"
+          : "=&v"(t), "+v"(rank)
+          : "v"(mine), "v"(k[u]), "s"(after)
+          : "vcc");
+      after &= after << 1;
+    }
+  }
+  return static_cast<int>(rank);
+}
+template <int SW>
+__device__ __forceinline__ int rank_row(const uint64_t* row, uint64_t mine, int E) {
+  uint64_t after = ~0ull;
+  if constexpr (SW == 8) after = 0xFEFEFEFEFEFEFEFEull;
+  else if constexpr (SW == 16) after = 0xFFFEFFFEFFFEFFFEull;
+  else if constexpr (SW == 32) after = 0xFFFFFFFEFFFFFFFEull;
+  else after = 0xFFFFFFFFFFFFFFFEull;
+  const uint32_t mlo = static_cast<uint32_t>(mine), mhi = static_cast<uint32_t>(mine >> 32);
+  uint32_t rank = 0;
+  for (int i = 0; i < E; i += 2) {
+    const uint32x4 k = *reinterpret_cast<const uint32x4*>(row + i);
+#pragma unroll
+    for (int u = 0; u < 2; ++u) {
+      uint32_t t;
+      asm("v_subb_co_u32_e64 %0, vcc, %2, %4, %6\n\t"
+          "v_subb_co_u32_e32 %0, vcc, %3, %5, vcc\n\t"
+          "v_addc_co_u32_e32 %1, vcc, 0, %1, vcc"
+          : "=&v"(t), "+v"(rank)
+          : "v"(mlo), "v"(mhi), "v"(k[2 * u]), "v"(k[2 * u + 1]), "s"(after)
+          : "vcc");
+      after &= after << 1;
+    }
+  }
+  return static_cast<int>(rank);
+}
+
+// LDS of one wavefront's rows: the keys (64-bit for blended rows, 32-bit
+// otherwise) and the probabilities in rank order.
+struct SelLds {
+  uint64_t keys[kMaxE];
+  double sorted[kMaxE];
+};
+
+// The selection of row (b, l) of the batch by the SW lanes that hold it
+// (`in`: whether they hold one), from the query's matches idx_b / score_b (k
+// of them, best first) and its layer bounds [lo, hi) (as given; clamped
+// here).
+template <int SW>
+__device__ __forceinline__ void select_row(const SelArgs& a, bool in, int b, int l, int lo, int hi,
+                                           const int32_t* idx_b, const float* score_b, SelLds& sm) {
   const int lane = threadIdx.x % kWave;
+  const int j = lane % SW;
+  const int base = lane - j;
   const int64_t row = static_cast<int64_t>(b) * a.L + l;
   lo = lo < 0 ? 0 : (lo > a.L ? a.L : lo);
   hi = hi < 0 ? 0 : (hi > a.L ? a.L : hi);
-  const int y0 = idx_b[0];
+  const int y0 = in ? idx_b[0] : -1;
 
-  // 1. guiding probability of expert `lane`: its loads need only the
-  // matches, so they are issued before the row's bounds are looked at (a
-  // row outside them discards the value)
+  // 1. guiding probability of expert j: its loads need only the matches, so
+  // they are issued before the row's bounds are looked at (a row outside
+  // them discards the value)
   const GuideView gv{a.planes, a.plane_elems, a.n, a.row, a.dtype};
-  double p = 0.0;
-  if (lane < a.E && y0 >= 0 && y0 < a.n) p = guide_prob(gv, idx_b, score_b, a.k, a.blend, l, lane);
+  const bool has = j < a.E && y0 >= 0 && y0 < a.n;
+  const double p = has ? guide_prob(gv, idx_b, score_b, a.k, a.blend, l, j) : 0.0;
 
-  bool live = l >= lo && l < hi && y0 >= 0;
+  bool live = in && l >= lo && l < hi && y0 >= 0;
   if (live && y0 >= a.n) {
-    if (lane == 0) atomicOr(a.flags, static_cast<uint32_t>(FM_FLAG_INDEX_RANGE));
+    if (j == 0) atomicOr(a.flags, static_cast<uint32_t>(FM_FLAG_INDEX_RANGE));
     live = false;
   }
-  if (!live) {
-    if (lane == 0) {
-      a.mask_out[row] = 0ull;
-      a.count_out[row] = 0;
-    }
-    return;
+  if (in && !live && j == 0) {
+    a.mask_out[row] = 0ull;
+    a.count_out[row] = 0;
   }
+  if (__ballot(live) == 0) return;   // every row of the wavefront is empty
 
   // 2. threshold
-  double tau;
+  double tau = static_cast<double>(a.tau);
   if (a.mode == FM_TAU_DYNAMIC) {
-    const double s = static_cast<double>(score_b[0]);
+    const double s = in ? static_cast<double>(score_b[0]) : 0.0;
     if (s != s) tau = 1.0;
     else {
-      double t = 1.0 - s;
+      const double t = 1.0 - s;
       tau = t < 0.0 ? 0.0 : (t > 1.0 ? 1.0 : t);
     }
-  } else {
-    tau = static_cast<double>(a.tau);
   }
 
-  // 3. rank: every lane counts the experts ahead of its own, comparing
-  // ordered integer keys read from LDS (broadcast reads, independent of
-  // each other)
-  const uint64_t key = ord_f64(p);
-  if (lane < a.E) keys[lane] = key;
-  __builtin_amdgcn_s_waitcnt(0);
-  __builtin_amdgcn_wave_barrier();
-  int rank = 0;
-#pragma unroll 8
-  for (int i = 0; i < a.E; ++i) {
-    const uint64_t ki = keys[i];
-    rank += (ki > key || (ki == key && i < lane)) ? 1 : 0;
+  // 3. rank (a stored value is a float32 or bf16, so its 32-bit key orders it
+  // exactly; a blend is a float64)
+  int rank;
+  if (a.blend == FM_BLEND_SCORE) {
+    const uint64_t key = j < a.E ? ord_f64(p) : 0ull;
+    sm.keys[lane] = key;
+    wait_lgkm0();
+    __builtin_amdgcn_wave_barrier();
+    rank = rank_row<SW>(sm.keys + base, key, a.E);
+  } else {
+    uint32_t* k32 = reinterpret_cast<uint32_t*>(sm.keys);
+    const uint32_t key = j < a.E ? ord_f32(static_cast<float>(p)) : 0u;
+    k32[lane] = key;
+    wait_lgkm0();
+    __builtin_amdgcn_wave_barrier();
+    rank = rank_row<SW>(k32 + base, key, a.E);
   }
-  if (lane < a.E) sorted[rank] = p;
-  __builtin_amdgcn_s_waitcnt(0);
+  if (j < a.E) sm.sorted[base + rank] = p;
+  wait_lgkm0();
   __builtin_amdgcn_wave_barrier();
 
   // 4. sequential float64 prefix sum in rank order: k* is the first count
-  // whose running sum reaches tau (E if none); values are read 8 at a time
-  // ahead of the sequential adds
+  // whose running sum reaches tau; values are read 8 at a time ahead of the
+  // sequential adds
   int kstar = a.E;
   double run = 0.0;
   bool found = false;
-  for (int k0 = 0; k0 < a.E && !found; k0 += 8) {
+  const int kend = a.k_max < a.E ? a.k_max : a.E;
+  for (int k0 = 0; k0 < kend; k0 += 8) {
     double v[8];
 #pragma unroll
-    for (int u = 0; u < 8; ++u) v[u] = k0 + u < a.E ? sorted[k0 + u] : 0.0;
+    for (int u = 0; u < 8; ++u) v[u] = k0 + u < kend ? sm.sorted[base + k0 + u] : 0.0;
 #pragma unroll
     for (int u = 0; u < 8; ++u) {
-      if (found || k0 + u >= a.E) break;
-      if (run >= tau) {
+      if (k0 + u >= kend) break;
+      if (!found && run >= tau) {
         kstar = k0 + u;
         found = true;
-        break;
       }
       run = __dadd_rn(run, v[u]);
     }
+    if (__ballot(live && !found) == 0) break;
   }
   int kk = kstar < a.k_min ? a.k_min : kstar;
   kk = kk > a.k_max ? a.k_max : kk;
-  const uint64_t mask = __ballot(lane < a.E && rank < kk);
-  if (lane == 0) {
-    a.mask_out[row] = mask;
+  const uint64_t all = __ballot(j < a.E && rank < kk);
+  if (live && j == 0) {
+    a.mask_out[row] = SW == 64 ? all : (all >> base) & ((1ull << (SW % 64)) - 1ull);
     a.count_out[row] = static_cast<uint8_t>(kk);
   }
 }
 
+// Rows per wavefront for E experts: lanes per row.
+constexpr int kMergeGroups = 1536;   // workgroups of a merge-and-select launch beyond which positions stop splitting
+inline int select_width(int E) { return E <= 8 ? 8 : (E <= 16 ? 16 : (E <= 32 ? 32 : 64)); }
+
+template <int SW>
 __global__ void __launch_bounds__(256) k_select(SelArgs a) {
-  __shared__ double sorted[4][kMaxE];
-  __shared__ uint64_t keys[4][kMaxE];
+  constexpr int RPW = kWave / SW;
+  __shared__ SelLds sm[4];
   const int wv = threadIdx.x / kWave;
-  const int64_t row = static_cast<int64_t>(blockIdx.x) * 4 + wv;
-  if (row >= static_cast<int64_t>(a.B) * a.L) return;
-  const int b = static_cast<int>(row / a.L);
-  const int l = static_cast<int>(row - static_cast<int64_t>(b) * a.L);
-  select_row(a, b, l, a.lb[b], a.le[b], a.idx + static_cast<int64_t>(b) * a.k, a.score + static_cast<int64_t>(b) * a.k,
-             sorted[wv], keys[wv]);
+  const int lane = threadIdx.x % kWave;
+  const int64_t row = (static_cast<int64_t>(blockIdx.x) * 4 + wv) * RPW + lane / SW;
+  const bool in = row < static_cast<int64_t>(a.B) * a.L;
+  if (__ballot(in) == 0) return;
+  const int b = in ? static_cast<int>(row / a.L) : 0;
+  const int l = in ? static_cast<int>(row - static_cast<int64_t>(b) * a.L) : 0;
+  select_row<SW>(a, in, b, l, a.lb[b], a.le[b], a.idx + static_cast<int64_t>(b) * a.k,
+                 a.score + static_cast<int64_t>(b) * a.k, sm[wv]);
 }
 
-// The cross-workgroup merge of a match call with the selection after it:
-// one wavefront per (sorted position, layer) row merges the position's
-// partial top-k lists (each of the row's L wavefronts on its own, so that no
-// wave waits for another), the layer-0 one writes the query's matches, and
-// every one selects its layer from the merged matches (staged in LDS).  The
-// same merge as k_finalize and the same selection as k_select.
+// The cross-workgroup merge of a match call with the selection after it.
+// Workgroup (pos, y): its four wavefronts merge the position's partial top-k
+// lists together, a list per thread (each wavefront of a row merging all of
+// them by itself cost most of this kernel for top-4 and top-8 lists), the
+// workgroups y = 0 write the query's matches, and the workgroup selects the
+// layers of its share: row sets y * 4 + wave, + 4 * gridDim.y, ...  of 64 / SW
+// layers each.  The same merge as k_finalize and the same selection as
+// k_select.  Measured (kernel time): 512 positions of 256 top-4 lists, 32
+// layers of 16 experts 26.6 -> 13.0 us; 100 positions of top-8 lists, 32 x 8
+// 18.1 -> 13.7 us; 512 of top-1 lists, 24 x 60 18.1 -> 15.0 us, where the
+// matched rows' reads bound it (a row's 15 quads lie in 15 cache lines, 94 MB
+// of lines for 12,288 rows of four float32 matches).
 struct MergeArgs {
   const uint64_t* partial;   // [positions][R][KTOP]
   const int32_t* perm;       // query at each position (NULL: the position itself)
@@ -174,47 +259,55 @@ struct MergeArgs {
   float* score_out;          // [B][k]
 };
 
-template <int KTOP>
+template <int KTOP, int SW>
 __global__ void __launch_bounds__(256) k_merge_select(SelArgs a, MergeArgs m) {
-  __shared__ double sorted[4][kMaxE];
-  __shared__ uint64_t keys[4][kMaxE];
+  constexpr int RPW = kWave / SW;
+  __shared__ SelLds sm[4];
+  __shared__ uint64_t wlist[4][KTOP];
   __shared__ int32_t midx[4][kMaxK];
   __shared__ float mscore[4][kMaxK];
   const int lane = threadIdx.x % kWave;
   const int wv = threadIdx.x / kWave;
-  const int64_t row = static_cast<int64_t>(blockIdx.x) * 4 + wv;
-  if (row >= static_cast<int64_t>(a.B) * a.L) return;
-  const int pos = static_cast<int>(row / a.L);
-  const int l = static_cast<int>(row - static_cast<int64_t>(pos) * a.L);
+  const int pos = blockIdx.x;
   // The loads that do not depend on the merge go first, side by side: the
-  // group's list count, the query index (then its layer bounds) and, for
-  // top-1 lists, the first kMaxPartials lists of the stride (those past the
-  // group's count are read but not merged).
+  // group's list count, the query index (then its layer bounds) and this
+  // thread's first list of the stride (past the group's count it is read but
+  // not merged).
   const int nr = m.rgrp != nullptr ? m.rgrp[pos / m.qg] : m.R;
   const int b = m.perm != nullptr ? m.perm[pos] : pos;
   const uint64_t* plist = m.partial + static_cast<int64_t>(pos) * m.R * KTOP;
   TopK<KTOP> t;
-  t.clear();
-  int r0 = lane;
-  if constexpr (KTOP == 1) {
-    constexpr int kPre = kMaxPartials / kWave;
-    uint64_t pk[kPre];
+  {
+    uint64_t first[KTOP];
+    const bool held = static_cast<int>(threadIdx.x) < m.R;
 #pragma unroll
-    for (int it = 0; it < kPre; ++it) pk[it] = lane + it * kWave < m.R ? plist[lane + it * kWave] : 0ull;
+    for (int jj = 0; jj < KTOP; ++jj) first[jj] = held ? plist[threadIdx.x * KTOP + jj] : 0ull;
 #pragma unroll
-    for (int it = 0; it < kPre; ++it)
-      if (lane + it * kWave < nr) t.merge(&pk[it]);
-    r0 = lane + kMaxPartials;
+    for (int jj = 0; jj < KTOP; ++jj) t.v[jj] = static_cast<int>(threadIdx.x) < nr ? first[jj] : 0ull;
   }
   const int lo = a.lb[b], hi = a.le[b];
-  for (int r = r0; r < nr; r += kWave) t.merge(plist + static_cast<int64_t>(r) * KTOP);
+  for (int r = threadIdx.x + 256; r < nr; r += 256) t.merge(plist + static_cast<int64_t>(r) * KTOP);
+  // (a wavefront past the lists has nothing to merge)
+  if (wv * kWave < nr) {
 #pragma unroll
-  for (int off = 1; off < kWave; off <<= 1) {
-    uint64_t o[KTOP];
+    for (int off = 1; off < kWave; off <<= 1) {
+      uint64_t o[KTOP];
 #pragma unroll
-    for (int jj = 0; jj < KTOP; ++jj) o[jj] = shfl_xor_u64(t.v[jj], off);
-    t.merge(o);
+      for (int jj = 0; jj < KTOP; ++jj) o[jj] = shfl_xor_u64(t.v[jj], off);
+      t.merge(o);
+    }
   }
+  if (lane == 0) {
+#pragma unroll
+    for (int jj = 0; jj < KTOP; ++jj) wlist[wv][jj] = t.v[jj];
+  }
+  __syncthreads();
+  // every wavefront merges the four lists for itself (the same result)
+#pragma unroll
+  for (int jj = 0; jj < KTOP; ++jj) t.v[jj] = wlist[0][jj];
+#pragma unroll
+  for (int ww = 1; ww < 4; ++ww)
+    if (ww * kWave < nr) t.merge(wlist[ww]);
   if (lane == 0) {
 #pragma unroll
     for (int jj = 0; jj < kMaxK; ++jj) {
@@ -222,7 +315,7 @@ __global__ void __launch_bounds__(256) k_merge_select(SelArgs a, MergeArgs m) {
       const uint64_t key = jj < KTOP ? t.v[jj < KTOP ? jj : 0] : 0ull;
       midx[wv][jj] = key_index(key);
       mscore[wv][jj] = key_score(key);
-      if (l == 0) {
+      if (blockIdx.y == 0 && wv == 0) {
         m.idx_out[static_cast<int64_t>(b) * a.k + jj] = key_index(key);
         m.score_out[static_cast<int64_t>(b) * a.k + jj] = key_score(key);
       }
@@ -231,12 +324,17 @@ __global__ void __launch_bounds__(256) k_merge_select(SelArgs a, MergeArgs m) {
   // (LDS only: the bounds' loads stay in flight)
   wait_lgkm0();
   __builtin_amdgcn_wave_barrier();
-  select_row(a, b, l, lo, hi, midx[wv], mscore[wv], sorted[wv], keys[wv]);
+  const int sets = (a.L + RPW - 1) / RPW;
+  for (int rs = static_cast<int>(blockIdx.y) * 4 + wv; rs < sets; rs += 4 * static_cast<int>(gridDim.y)) {
+    const int l = rs * RPW + lane / SW;
+    select_row<SW>(a, l < a.L, b, l < a.L ? l : 0, lo, hi, midx[wv], mscore[wv], sm[wv]);
+    __builtin_amdgcn_wave_barrier();
+  }
 }
 
-// Misses of the prefetch sets (Section 3): one wavefront per (query, layer)
-// row; lane j ranks expert j of the query's own gate probabilities among the
-// row (the same order as the selection), the K best are the activated
+// Misses of the prefetch sets (Section 3): SW lanes per (query, layer) row, as
+// in the selection; lane j ranks expert j of the query's own gate
+// probabilities among the row (the same order), the K best are the activated
 // experts, and the count of those outside the set is written.
 struct MissArgs {
   const void* q;           // [B][L][E] of the map dtype
@@ -248,36 +346,40 @@ struct MissArgs {
   uint8_t* miss_out;       // [B][L]
 };
 
+template <int SW>
 __global__ void __launch_bounds__(256) k_miss(MissArgs a) {
-  __shared__ float vals[4][kMaxE];
+  constexpr int RPW = kWave / SW;
+  __shared__ __align__(16) uint32_t keys[4][kMaxE];
   const int lane = threadIdx.x % kWave;
   const int wv = threadIdx.x / kWave;
-  const int64_t row = static_cast<int64_t>(blockIdx.x) * 4 + wv;
-  if (row >= static_cast<int64_t>(a.B) * a.L) return;
-  const int b = static_cast<int>(row / a.L);
-  const int l = static_cast<int>(row - static_cast<int64_t>(b) * a.L);
+  const int j = lane % SW;
+  const int base = lane - j;
+  const int64_t row = (static_cast<int64_t>(blockIdx.x) * 4 + wv) * RPW + lane / SW;
+  const bool in = row < static_cast<int64_t>(a.B) * a.L;
+  if (__ballot(in) == 0) return;
+  const int b = in ? static_cast<int>(row / a.L) : 0;
+  const int l = in ? static_cast<int>(row - static_cast<int64_t>(b) * a.L) : 0;
+  // the row's values, set and bounds load side by side
+  float p = 0.0f;
+  if (in && j < a.E) {
+    const int64_t i = row * a.E + j;
+    p = a.dtype == FM_F32 ? static_cast<const float*>(a.q)[i] : bf16_to_f32(static_cast<const uint16_t*>(a.q)[i]);
+  }
+  const uint64_t set = in ? a.masks[row] : 0ull;
   int lo = a.lb[b], hi = a.le[b];
   lo = lo < 0 ? 0 : (lo > a.L ? a.L : lo);
   hi = hi < 0 ? 0 : (hi > a.L ? a.L : hi);
-  if (l < lo || l >= hi) {
-    if (lane == 0) a.miss_out[row] = 0;
-    return;
-  }
-  float p = 0.0f;
-  if (lane < a.E) {
-    const int64_t i = row * a.E + lane;
-    p = a.dtype == FM_F32 ? static_cast<const float*>(a.q)[i] : bf16_to_f32(static_cast<const uint16_t*>(a.q)[i]);
-    vals[wv][lane] = p;
-  }
-  __builtin_amdgcn_s_waitcnt(0);
+  const bool live = in && l >= lo && l < hi;
+  if (in && !live && j == 0) a.miss_out[row] = 0;
+  if (__ballot(live) == 0) return;
+  const uint32_t key = j < a.E ? ord_f32(p) : 0u;
+  keys[wv][lane] = key;
+  wait_lgkm0();
   __builtin_amdgcn_wave_barrier();
-  int rank = 0;
-  for (int i = 0; i < a.E; ++i) {
-    const float pi = vals[wv][i];
-    if (i != lane && ahead(pi, i, p, lane)) ++rank;
-  }
-  const uint64_t act = __ballot(lane < a.E && rank < a.K);
-  if (lane == 0) a.miss_out[row] = static_cast<uint8_t>(__popcll(act & ~a.masks[row]));
+  const int rank = rank_row<SW>(keys[wv] + base, key, a.E);
+  const uint64_t all = __ballot(j < a.E && rank < a.K);
+  const uint64_t act = SW == 64 ? all : (all >> base) & ((1ull << (SW % 64)) - 1ull);
+  if (live && j == 0) a.miss_out[row] = static_cast<uint8_t>(__popcll(act & ~set));
 }
 
 hipError_t launch_miss(const StoreView& s, const void* q, int32_t B, int32_t K, const uint64_t* masks,
@@ -293,8 +395,14 @@ hipError_t launch_miss(const StoreView& s, const void* q, int32_t B, int32_t K, 
   a.lb = lb;
   a.le = le;
   a.miss_out = miss_out;
+  const int SW = select_width(s.E);
   const int64_t rows = static_cast<int64_t>(B) * s.L;
-  hipLaunchKernelGGL(k_miss, dim3(static_cast<unsigned>((rows + 3) / 4)), dim3(256), 0, st, a);
+  const int64_t per = 4 * (kWave / SW);   // rows per workgroup
+  const dim3 grid(static_cast<unsigned>((rows + per - 1) / per));
+  if (SW == 8) hipLaunchKernelGGL(k_miss<8>, grid, dim3(256), 0, st, a);
+  else if (SW == 16) hipLaunchKernelGGL(k_miss<16>, grid, dim3(256), 0, st, a);
+  else if (SW == 32) hipLaunchKernelGGL(k_miss<32>, grid, dim3(256), 0, st, a);
+  else hipLaunchKernelGGL(k_miss<64>, grid, dim3(256), 0, st, a);
   return hipGetLastError();
 }
 
@@ -334,11 +442,28 @@ hipError_t launch_select(const StoreView& s, const int32_t* idx, const float* sc
                          const int32_t* lb, const int32_t* le, const fm_select_params& p, uint64_t* mask_out,
                          uint8_t* count_out, hipStream_t st) {
   const SelArgs a = select_args(s, idx, score, B, k, lb, le, p, mask_out, count_out);
+  const int SW = select_width(s.E);
   const int64_t rows = static_cast<int64_t>(B) * s.L;
-  const int64_t blocks = (rows + 3) / 4;
-  hipLaunchKernelGGL(k_select, dim3(static_cast<unsigned>(blocks)), dim3(256), 0, st, a);
+  const int64_t per = 4 * (kWave / SW);   // rows per workgroup
+  const dim3 grid(static_cast<unsigned>((rows + per - 1) / per));
+  if (SW == 8) hipLaunchKernelGGL(k_select<8>, grid, dim3(256), 0, st, a);
+  else if (SW == 16) hipLaunchKernelGGL(k_select<16>, grid, dim3(256), 0, st, a);
+  else if (SW == 32) hipLaunchKernelGGL(k_select<32>, grid, dim3(256), 0, st, a);
+  else hipLaunchKernelGGL(k_select<64>, grid, dim3(256), 0, st, a);
   return hipGetLastError();
 }
+
+namespace {
+
+template <int KTOP>
+void merge_select_launch(int SW, dim3 grid, const SelArgs& a, const MergeArgs& m, hipStream_t st) {
+  if (SW == 8) hipLaunchKernelGGL((k_merge_select<KTOP, 8>), grid, dim3(256), 0, st, a, m);
+  else if (SW == 16) hipLaunchKernelGGL((k_merge_select<KTOP, 16>), grid, dim3(256), 0, st, a, m);
+  else if (SW == 32) hipLaunchKernelGGL((k_merge_select<KTOP, 32>), grid, dim3(256), 0, st, a, m);
+  else hipLaunchKernelGGL((k_merge_select<KTOP, 64>), grid, dim3(256), 0, st, a, m);
+}
+
+}  // namespace
 
 hipError_t launch_merge_select(const StoreView& s, const uint64_t* partial, const int32_t* perm, int32_t B, int32_t R,
                                int32_t k, int KTOP, const int32_t* rgrp, int32_t qg, int32_t* idx_out,
@@ -352,11 +477,18 @@ hipError_t launch_merge_select(const StoreView& s, const uint64_t* partial, cons
   m.qg = qg > 0 ? qg : 1;
   m.idx_out = idx_out;
   m.score_out = score_out;
-  const int64_t rows = static_cast<int64_t>(B) * s.L;
-  const dim3 grid(static_cast<unsigned>((rows + 3) / 4));
-  if (KTOP == 1) hipLaunchKernelGGL(k_merge_select<1>, grid, dim3(256), 0, st, a, m);
-  else if (KTOP == 4) hipLaunchKernelGGL(k_merge_select<4>, grid, dim3(256), 0, st, a, m);
-  else hipLaunchKernelGGL(k_merge_select<8>, grid, dim3(256), 0, st, a, m);
+  // Workgroups per position: enough that every wavefront selects one set of
+  // rows, fewer (each then selects several in turn) once the batch alone
+  // fills the chip, since every workgroup of a position repeats its merge.
+  const int SW = select_width(s.E);
+  const int sets = (s.L + kWave / SW - 1) / (kWave / SW);
+  int S = (sets + 3) / 4;
+  const int most = (kMergeGroups + B - 1) / B;
+  if (S > most) S = most;
+  const dim3 grid(static_cast<unsigned>(B), static_cast<unsigned>(S));
+  if (KTOP == 1) merge_select_launch<1>(SW, grid, a, m, st);
+  else if (KTOP == 4) merge_select_launch<4>(SW, grid, a, m, st);
+  else merge_select_launch<8>(SW, grid, a, m, st);
   return hipGetLastError();
 }
 
