@@ -345,7 +345,9 @@ fm_status fm_traj_step(fm_store* store, void* state, size_t state_bytes, const v
 
 /* Test support: the dense float32 score matrix of a trajectory (q, depth
  * non-NULL) or semantic (q_sem non-NULL) search, written to scores_out device
- * [B][size] by the same kernels and arithmetic as the match calls.
+ * [B][size] with the arithmetic of the match calls (the same kernels, but for
+ * semantic searches of a size that the match calls run on their split-k scan,
+ * whose float32 sums are taken in another order).
  * Exactly one of q / q_sem must be non-NULL. */
 fm_status fm_debug_scores(const fm_store* store, const void* q, const int32_t* depth,
                           int32_t max_depth, const void* q_sem, int32_t B, float* scores_out,
@@ -354,7 +356,7 @@ fm_status fm_debug_scores(const fm_store* store, const void* q, const int32_t* d
 /* Measurement support: start and stop are hipEvent_t handles (passed as
  * void*) created by the caller, or both NULL to switch this off.  While set,
  * every match call made on this thread records start on its stream right
- * before the launch of its scan kernel (k_traj_scan or k_sem_scan; k_traj_step
+ * before the launch of its scan kernel (k_traj_* or k_sem_*; k_traj_step
  * for fm_traj_step) and stop right after it, so the events bracket exactly
  * that kernel (for a batch of more than one launch, the last launch's).  The library does not own or
  * destroy the events.  FM_ERR_INVALID if exactly one of them is NULL. */

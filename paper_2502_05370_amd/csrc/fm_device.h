@@ -97,6 +97,22 @@ __device__ __forceinline__ float key_score(uint64_t key) {
   return key == 0 ? -__builtin_inff() : unord_score(static_cast<uint32_t>(key >> 32));
 }
 
+// The jj-th match of a merged list whose keys rank by dot / |x|, given rq =
+// 1/|q|: the factor is positive and leaves the order alone.  rq = 0 is a zero
+// query (every dot 0, so the list is the lowest indices) or one with an
+// infinity, whose every cosine is NaN: its dots are infinite or NaN, and its
+// matches are the lowest indices of the n stored ones.
+__device__ __forceinline__ void scale_match(uint64_t key, uint64_t key0, float rq, int32_t n, int jj, int32_t& idx,
+                                            float& score) {
+  idx = key_index(key);
+  score = key == 0 ? -__builtin_inff() : key_score(key) * rq;
+  const float top = key_score(key0);
+  if (key0 != 0 && rq == 0.0f && !(__builtin_fabsf(top) < __builtin_inff())) {
+    idx = jj < n ? jj : -1;
+    score = jj < n ? __builtin_nanf("") : -__builtin_inff();
+  }
+}
+
 __device__ __forceinline__ uint64_t shfl_xor_u64(uint64_t v, int m) {
   uint32_t lo = __shfl_xor(static_cast<uint32_t>(v), m, kWave);
   uint32_t hi = __shfl_xor(static_cast<uint32_t>(v >> 32), m, kWave);

@@ -84,10 +84,12 @@ DedupScratch carve_dedup_scratch(void* base, int32_t cap, int32_t n_max);
 Workspace carve_workspace(void* base);
 size_t traj_qrows_bytes(int L, int E, fm_dtype dt, int b_pad);
 // partial holds R lists per position; with rgrp set, position pos merges only
-// the first rgrp[pos / qg] of them.
+// the first rgrp[pos / qg] of them.  With rq set, the lists rank by
+// dot / |x| and the scores written are that times rq[pos] = 1/|q| (n: the
+// store's size).
 hipError_t launch_finalize(const uint64_t* partial, const int32_t* perm, int32_t B, int32_t R, int32_t k, int KTOP,
                            int32_t* idx_out, float* score_out, hipStream_t st, const int32_t* rgrp = nullptr,
-                           int32_t qg = 0);
+                           int32_t qg = 0, const float* rq = nullptr, int32_t n = 0);
 
 // Caller-provided events bracketing the next scan launches on this thread
 // (both null when unset); see fm_debug_scan_events.
@@ -125,7 +127,7 @@ struct SelectFuse {
 // matches written to idx_out / score_out, then each row's selection.
 hipError_t launch_merge_select(const StoreView& s, const uint64_t* partial, const int32_t* perm, int32_t B, int32_t R,
                                int32_t k, int KTOP, const int32_t* rgrp, int32_t qg, int32_t* idx_out,
-                               float* score_out, const SelectFuse& f, hipStream_t st);
+                               float* score_out, const SelectFuse& f, hipStream_t st, const float* rq = nullptr);
 // With fuse set, the merge of each launch is the merge-and-select above.
 hipError_t launch_match_trajectory(const StoreView& s, const void* q, const int32_t* depth,
                                    int32_t max_depth, int32_t B, int32_t k, int32_t* idx_out,
@@ -145,6 +147,20 @@ hipError_t launch_match_semantic(const StoreView& s, const void* q, int32_t B, i
 int sem_mm_group(int32_t Bc);
 hipError_t launch_sem_mm(const StoreView& s, int32_t Bc, int32_t b_pad, const Workspace& ws, float* dbg, int32_t* R_out,
                          hipStream_t st, const float* mix = nullptr, double w_self = 1.0, double w_mix = 0.0);
+// Split-k semantic scan (fm_sem_split.hip): whether and how a chunk of Bc
+// queries takes it (shape < 0: it takes k_sem_mm), and the scan itself, on
+// queries staged by k_sem_prep in groups of p.group or, with p.raw, on the
+// caller's rows.  Its partial lists (p.R per query) rank by dot / |x|; their
+// merge takes ws.rq as rq.
+struct SemSplit {
+  int shape = -1;
+  bool raw = false;   // reads the caller's rows and writes ws.rq itself
+  int group = 0;      // queries per group
+  int R = 0;          // partial lists per query
+};
+SemSplit sem_split_plan(int32_t Bc, int32_t n, int32_t d, int KTOP);
+hipError_t launch_sem_split(const StoreView& s, const SemSplit& p, const uint16_t* q, int32_t Bc, int KTOP,
+                            const Workspace& ws, hipStream_t st);
 // Top-1 trajectory scan of bf16 stores (fm_traj_mm.hip): whether a chunk of
 // Bc queries takes it, its queries per group, and the scan itself on queries
 // staged by k_traj_prep in its tiled layout (b_pad = groups * queries per

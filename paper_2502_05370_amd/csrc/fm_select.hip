@@ -257,6 +257,7 @@ struct MergeArgs {
   int32_t qg;                // positions per query group
   int32_t* idx_out;          // [B][k]
   float* score_out;          // [B][k]
+  const float* rq;           // 1/|q| per position, for lists that rank by dot / |x| (NULL: the keys hold the scores)
 };
 
 template <int KTOP, int SW>
@@ -286,6 +287,7 @@ __global__ void __launch_bounds__(256) k_merge_select(SelArgs a, MergeArgs m) {
     for (int jj = 0; jj < KTOP; ++jj) t.v[jj] = static_cast<int>(threadIdx.x) < nr ? first[jj] : 0ull;
   }
   const int lo = a.lb[b], hi = a.le[b];
+  const float rq = m.rq != nullptr ? m.rq[pos] : 1.0f;
   for (int r = threadIdx.x + 256; r < nr; r += 256) t.merge(plist + static_cast<int64_t>(r) * KTOP);
   // (a wavefront past the lists has nothing to merge)
   if (wv * kWave < nr) {
@@ -313,11 +315,14 @@ __global__ void __launch_bounds__(256) k_merge_select(SelArgs a, MergeArgs m) {
     for (int jj = 0; jj < kMaxK; ++jj) {
       if (jj >= a.k) break;
       const uint64_t key = jj < KTOP ? t.v[jj < KTOP ? jj : 0] : 0ull;
-      midx[wv][jj] = key_index(key);
-      mscore[wv][jj] = key_score(key);
+      int32_t y = key_index(key);
+      float sc = key_score(key);
+      if (m.rq != nullptr) scale_match(key, t.v[0], rq, a.n, jj, y, sc);
+      midx[wv][jj] = y;
+      mscore[wv][jj] = sc;
       if (blockIdx.y == 0 && wv == 0) {
-        m.idx_out[static_cast<int64_t>(b) * a.k + jj] = key_index(key);
-        m.score_out[static_cast<int64_t>(b) * a.k + jj] = key_score(key);
+        m.idx_out[static_cast<int64_t>(b) * a.k + jj] = y;
+        m.score_out[static_cast<int64_t>(b) * a.k + jj] = sc;
       }
     }
   }
@@ -467,7 +472,7 @@ void merge_select_launch(int SW, dim3 grid, const SelArgs& a, const MergeArgs& m
 
 hipError_t launch_merge_select(const StoreView& s, const uint64_t* partial, const int32_t* perm, int32_t B, int32_t R,
                                int32_t k, int KTOP, const int32_t* rgrp, int32_t qg, int32_t* idx_out,
-                               float* score_out, const SelectFuse& f, hipStream_t st) {
+                               float* score_out, const SelectFuse& f, hipStream_t st, const float* rq) {
   const SelArgs a = select_args(s, nullptr, nullptr, B, k, f.lb, f.le, f.p, f.mask_out, f.count_out);
   MergeArgs m;
   m.partial = partial;
@@ -477,6 +482,7 @@ hipError_t launch_merge_select(const StoreView& s, const uint64_t* partial, cons
   m.qg = qg > 0 ? qg : 1;
   m.idx_out = idx_out;
   m.score_out = score_out;
+  m.rq = rq;
   // Workgroups per position: enough that every wavefront selects one set of
   // rows, fewer (each then selects several in turn) once the batch alone
   // fills the chip, since every workgroup of a position repeats its merge.

@@ -5,8 +5,9 @@
 // contraction over the hidden size on bf16 MFMA
 // (v_mfma_f32_16x16x32_bf16: exact bf16 products, float32 accumulation).
 // Stored embeddings are kept as 1 KB MFMA operand tiles (emb_offset), so every
-// operand load is one contiguous 1 KB read.  A batch of up to 1024 queries is
-// served by three launches:
+// operand load is one contiguous 1 KB read.  A batch of up to 1024 queries
+// that keeps 2 to 8 matches is served by three launches (one match:
+// fm_sem_mm.hip; small searches: fm_sem_split.hip):
 //
 //  k_sem_prep   copies the queries into the same tile layout (zero rows pad
 //               the last 16-query tile) and writes 1/|q| (float64 sum).
@@ -44,11 +45,6 @@ struct SemArgs {
   int32_t n_blocks;      // 16-map blocks of the store
   int32_t grid;
   Workspace ws;
-  float* dbg;            // optional dense scores [B][n]
-  // Optional second dense matrix [B][n]: when set, the dense output is the
-  // weighted sum w_self * score + w_mix * mix (float64, rounded once).
-  const float* mix;
-  double w_self, w_mix;
 };
 
 // Position of stage j of the semantic scan: slice j / NKC, k-step pair
@@ -107,7 +103,7 @@ __global__ void __launch_bounds__(256) k_sem_prep(SemPrepArgs a) {
 // the count fixed), so "stage j+1 has landed" is vmcnt <= the loads of two
 // stages at the end of stage j.  Slot (j+3) % 4 was last read in stage j-1,
 // which every wave finished before the barrier of stage j.
-template <int TQ, int KTOP, bool DBG>
+template <int TQ, int KTOP>
 __global__ void __launch_bounds__(512) k_sem_scan(SemArgs a) {
   constexpr int W = 8;                        // waves per workgroup
   constexpr int NBA = 2;                      // 16-map blocks per wave and slice
@@ -338,14 +334,6 @@ __global__ void __launch_bounds__(512) k_sem_scan(SemArgs a) {
               if (y >= a.n) continue;
               const float rx = xn[i] > 0.0f ? 1.0f / xn[i] : (xn[i] != xn[i] ? xn[i] : 0.0f);
               const float s = acc[nb][t][i] * rq * rx;
-              if constexpr (DBG) {
-                const int64_t o = static_cast<int64_t>(b) * a.n + y;
-                float v = s;
-                if (a.mix != nullptr)
-                  v = static_cast<float>(__dadd_rn(__dmul_rn(a.w_self, static_cast<double>(s)),
-                                                   __dmul_rn(a.w_mix, static_cast<double>(a.mix[o]))));
-                a.dbg[o] = v;
-              }
               best[t].push(make_key(s, y));
             }
           }
@@ -417,8 +405,8 @@ __global__ void __launch_bounds__(512) k_sem_scan(SemArgs a) {
 
 namespace {
 
-// Largest query-tile count per workgroup for each list size (registers).
-constexpr int sem_tq_limit(int ktop) { return ktop == 1 ? 8 : 4; }
+// Query tiles per workgroup (registers).
+constexpr int kSemTq = 4;
 
 // LDS: four query ring slots and the query norms; the merge buffer reuses
 // the ring.
@@ -429,10 +417,10 @@ size_t sem_lds(int TQ, int KTOP) {
   return ring + static_cast<size_t>(16) * TQ * 4;
 }
 
-template <int TQ, int KTOP, bool DBG = false>
+template <int TQ, int KTOP>
 hipError_t sem_launch(const SemArgs& a, hipStream_t st) {
   const size_t lds = sem_lds(TQ, KTOP);
-  auto kern = k_sem_scan<TQ, KTOP, DBG>;
+  auto kern = k_sem_scan<TQ, KTOP>;
   if (lds > 64 * 1024) {
     const hipError_t err = hipFuncSetAttribute(reinterpret_cast<const void*>(kern),
                                                hipFuncAttributeMaxDynamicSharedMemorySize, static_cast<int>(lds));
@@ -449,18 +437,14 @@ hipError_t sem_launch(const SemArgs& a, hipStream_t st) {
   return hipEventRecord(ev.stop, st);
 }
 
-template <int KTOP, bool DBG = false>
+template <int KTOP>
 hipError_t sem_tq(int TQ, const SemArgs& a, hipStream_t st) {
   switch (TQ) {
-    case 1: return sem_launch<1, KTOP, DBG>(a, st);
-    case 2: return sem_launch<2, KTOP, DBG>(a, st);
-    case 4: return sem_launch<4, KTOP, DBG>(a, st);
-    case 8:
-      if constexpr (sem_tq_limit(KTOP) >= 8) return sem_launch<8, KTOP, DBG>(a, st);
-      break;
-    default: break;
+    case 1: return sem_launch<1, KTOP>(a, st);
+    case 2: return sem_launch<2, KTOP>(a, st);
+    case 4: return sem_launch<4, KTOP>(a, st);
+    default: return hipErrorInvalidValue;
   }
-  return hipErrorInvalidValue;
 }
 
 }  // namespace
@@ -469,19 +453,19 @@ hipError_t launch_match_semantic(const StoreView& s, const void* q, int32_t B, i
                                  float* score_out, float* dbg_scores, const Workspace& ws, hipStream_t st,
                                  const float* mix, double w_self, double w_mix, const SelectFuse* fuse) {
   const int KTOP = k == 1 ? 1 : (k <= 4 ? 4 : 8);
-  // the dense-output form keeps top-1 lists (k = 1)
-  const int tq_max = sem_tq_limit(dbg_scores != nullptr ? 1 : KTOP);
   const int n_blocks = (s.n + 15) / 16;
-  // top-1 searches and the dense form (which keeps no lists there) run on
-  // the 128 x 128 wave-tile scan (fm_sem_mm.hip); lists of 4 or 8, and a
-  // dense form that also returns matches, on the general scan
-  const bool mm = dbg_scores != nullptr ? idx_out == nullptr : KTOP == 1 && mix == nullptr;
+  // The dense form (no matches returned) runs on k_sem_mm (fm_sem_mm.hip); a
+  // search on the split-k scan where that is the faster one
+  // (fm_sem_split.hip), else one match on k_sem_mm and lists of 4 or 8 here.
+  const bool mm = dbg_scores != nullptr || KTOP == 1;
   for (int b0 = 0; b0 < B; b0 += kChunkB) {
     const int Bc = (B - b0) < kChunkB ? (B - b0) : kChunkB;
     int TQ = 1;
-    while (16 * TQ < Bc && TQ < tq_max) TQ *= 2;
+    while (16 * TQ < Bc && TQ < kSemTq) TQ *= 2;
     if (mm) TQ = sem_mm_group(Bc) / 16;
-    const int QG = 16 * TQ;
+    SemSplit sp;
+    if (dbg_scores == nullptr) sp = sem_split_plan(Bc, s.n, s.d_emb, KTOP);
+    const int QG = sp.shape >= 0 ? sp.group : 16 * TQ;
     const int n_qg = (Bc + QG - 1) / QG;
     const int b_pad = n_qg * QG;
 
@@ -492,9 +476,24 @@ hipError_t launch_match_semantic(const StoreView& s, const void* q, int32_t B, i
     pa.b_pad = b_pad;
     pa.qst = static_cast<uint16_t*>(ws.qrows);
     pa.rq = ws.rq;
-    hipLaunchKernelGGL(k_sem_prep, dim3((b_pad + 3) / 4), dim3(256), 0, st, pa);
-    hipError_t err = hipGetLastError();
-    if (err != hipSuccess) return err;
+    hipError_t err = hipSuccess;
+    if (!sp.raw) {
+      hipLaunchKernelGGL(k_sem_prep, dim3((b_pad + 3) / 4), dim3(256), 0, st, pa);
+      err = hipGetLastError();
+      if (err != hipSuccess) return err;
+    }
+    if (sp.shape >= 0) {
+      err = launch_sem_split(s, sp, pa.q, Bc, KTOP, ws, st);
+      if (err != hipSuccess) return err;
+      err = fuse != nullptr
+                ? launch_merge_select(s, ws.partial, nullptr, Bc, sp.R, k, KTOP, nullptr, 0,
+                                      idx_out + static_cast<int64_t>(b0) * k, score_out + static_cast<int64_t>(b0) * k,
+                                      fuse->at(b0, s.L), st, ws.rq)
+                : launch_finalize(ws.partial, nullptr, Bc, sp.R, k, KTOP, idx_out + static_cast<int64_t>(b0) * k,
+                                  score_out + static_cast<int64_t>(b0) * k, st, nullptr, 0, ws.rq, s.n);
+      if (err != hipSuccess) return err;
+      continue;
+    }
 
     if (mm) {
       int R = 1;
@@ -532,24 +531,15 @@ hipError_t launch_match_semantic(const StoreView& s, const void* q, int32_t B, i
     a.n_blocks = n_blocks;
     a.grid = (n_qg * R + 7) / 8 * 8;
     a.ws = ws;
-    a.dbg = dbg_scores != nullptr ? dbg_scores + static_cast<int64_t>(b0) * s.n : nullptr;
-    a.mix = mix != nullptr ? mix + static_cast<int64_t>(b0) * s.n : nullptr;
-    a.w_self = w_self;
-    a.w_mix = w_mix;
-    if (dbg_scores != nullptr) err = sem_tq<1, true>(TQ, a, st);
-    else if (KTOP == 1) err = sem_tq<1>(TQ, a, st);
-    else if (KTOP == 4) err = sem_tq<4>(TQ, a, st);
-    else err = sem_tq<8>(TQ, a, st);
+    err = KTOP == 4 ? sem_tq<4>(TQ, a, st) : sem_tq<8>(TQ, a, st);
     if (err != hipSuccess) return err;
-    if (idx_out != nullptr) {
-      err = fuse != nullptr
-                ? launch_merge_select(s, ws.partial, nullptr, Bc, R, k, KTOP, nullptr, 0,
-                                      idx_out + static_cast<int64_t>(b0) * k, score_out + static_cast<int64_t>(b0) * k,
-                                      fuse->at(b0, s.L), st)
-                : launch_finalize(ws.partial, nullptr, Bc, R, k, KTOP, idx_out + static_cast<int64_t>(b0) * k,
-                                  score_out + static_cast<int64_t>(b0) * k, st);
-      if (err != hipSuccess) return err;
-    }
+    err = fuse != nullptr
+              ? launch_merge_select(s, ws.partial, nullptr, Bc, R, k, KTOP, nullptr, 0,
+                                    idx_out + static_cast<int64_t>(b0) * k, score_out + static_cast<int64_t>(b0) * k,
+                                    fuse->at(b0, s.L), st)
+              : launch_finalize(ws.partial, nullptr, Bc, R, k, KTOP, idx_out + static_cast<int64_t>(b0) * k,
+                                score_out + static_cast<int64_t>(b0) * k, st);
+    if (err != hipSuccess) return err;
   }
   return hipSuccess;
 }

@@ -4,7 +4,8 @@
 // (B x d) with the stored embeddings (n x d), both bf16, on
 // v_mfma_f32_16x16x32_bf16 (exact bf16 products, float32 accumulation),
 // followed by the cosine scaling and the best stored index per query.  This
-// kernel serves searches that keep one match per query and the dense form
+// kernel serves searches that keep one match per query, but for the small
+// ones that the split-k scan takes (fm_sem_split.hip), and the dense form
 // (every cosine, or its weighted sum with a second dense matrix: the
 // deduplicating insert's RDY); k_sem_scan (fm_sem.hip) serves top-2..8
 // lists.  k_sem_prep stages the queries in the embedding tile layout and

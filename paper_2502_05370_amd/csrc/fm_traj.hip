@@ -883,7 +883,7 @@ template <int KTOP>
 __global__ void __launch_bounds__(256) k_finalize(const uint64_t* __restrict__ partial, const int32_t* __restrict__ perm,
                                                   int32_t B, int32_t R, int32_t k, int32_t* __restrict__ idx_out,
                                                   float* __restrict__ score_out, const int32_t* __restrict__ rgrp,
-                                                  int32_t qg) {
+                                                  int32_t qg, const float* __restrict__ rq, int32_t n) {
   const int lane = threadIdx.x % kWave;
   const int pos = blockIdx.x * (blockDim.x / kWave) + threadIdx.x / kWave;
   if (pos >= B) return;
@@ -904,21 +904,28 @@ __global__ void __launch_bounds__(256) k_finalize(const uint64_t* __restrict__ p
     for (int jj = 0; jj < kMaxK; ++jj) {
       if (jj >= k) break;
       const uint64_t key = jj < KTOP ? m.v[jj < KTOP ? jj : 0] : 0ull;
-      idx_out[static_cast<int64_t>(b) * k + jj] = key_index(key);
-      score_out[static_cast<int64_t>(b) * k + jj] = key_score(key);
+      int32_t y = key_index(key);
+      float sc = key_score(key);
+      if (rq != nullptr) scale_match(key, m.v[0], rq[pos], n, jj, y, sc);
+      idx_out[static_cast<int64_t>(b) * k + jj] = y;
+      score_out[static_cast<int64_t>(b) * k + jj] = sc;
     }
   }
 }
 
 hipError_t launch_finalize(const uint64_t* partial, const int32_t* perm, int32_t B, int32_t R, int32_t k, int KTOP,
-                           int32_t* idx_out, float* score_out, hipStream_t st, const int32_t* rgrp, int32_t qg) {
+                           int32_t* idx_out, float* score_out, hipStream_t st, const int32_t* rgrp, int32_t qg,
+                           const float* rq, int32_t n) {
   const dim3 grid((B + kWaves - 1) / kWaves);
   if (KTOP == 1)
-    hipLaunchKernelGGL(k_finalize<1>, grid, dim3(kThreads), 0, st, partial, perm, B, R, k, idx_out, score_out, rgrp, qg);
+    hipLaunchKernelGGL(k_finalize<1>, grid, dim3(kThreads), 0, st, partial, perm, B, R, k, idx_out, score_out, rgrp, qg, rq,
+                       n);
   else if (KTOP == 4)
-    hipLaunchKernelGGL(k_finalize<4>, grid, dim3(kThreads), 0, st, partial, perm, B, R, k, idx_out, score_out, rgrp, qg);
+    hipLaunchKernelGGL(k_finalize<4>, grid, dim3(kThreads), 0, st, partial, perm, B, R, k, idx_out, score_out, rgrp, qg, rq,
+                       n);
   else
-    hipLaunchKernelGGL(k_finalize<8>, grid, dim3(kThreads), 0, st, partial, perm, B, R, k, idx_out, score_out, rgrp, qg);
+    hipLaunchKernelGGL(k_finalize<8>, grid, dim3(kThreads), 0, st, partial, perm, B, R, k, idx_out, score_out, rgrp, qg, rq,
+                       n);
   return hipGetLastError();
 }
 
