@@ -93,14 +93,14 @@ ScanEvents& scan_events() {
   return ev;
 }
 
-// Workspace layout: [partial][perm][sdep][rq][pgrp][rgrp][ngrp][qrows], each part 256-byte
+// Workspace layout: [partial][perm][sdep][rq][pgrp][rgrp][ngrp][floor][qrows], each part 256-byte
 // aligned.  qrows holds the staged queries of one launch: the trajectory
 // planes, or the tiled semantic queries (1024 x d_emb bf16).
 
 // Parts before the staged queries (partial lists, positions, groups).
 static size_t workspace_fixed_bytes() {
   size_t b = align_up(sizeof(uint64_t) * kChunkB * kMaxPartials * kMaxK, kAlign);
-  b += 3 * align_up(sizeof(int32_t) * kChunkB, kAlign);
+  b += 4 * align_up(sizeof(int32_t) * kChunkB, kAlign);
   b += 3 * align_up(sizeof(int32_t) * (kChunkB / 16), kAlign);
   return b;
 }
@@ -133,6 +133,8 @@ Workspace carve_workspace(void* base) {
   p += align_up(sizeof(int32_t) * (kChunkB / 16), kAlign);
   w.ngrp = reinterpret_cast<int32_t*>(p);
   p += align_up(sizeof(int32_t) * (kChunkB / 16), kAlign);
+  w.floor = reinterpret_cast<uint32_t*>(p);
+  p += align_up(sizeof(uint32_t) * kChunkB, kAlign);
   w.qrows = p;
   return w;
 }

@@ -63,6 +63,7 @@ struct Workspace {
   int32_t* pgrp;      // [kChunkB / 16] first scan workgroup of each query group (trajectory)
   int32_t* rgrp;      // [kChunkB / 16] scan workgroups (partial lists) of each query group
   int32_t* ngrp;      // [kChunkB / 16] layer groups each query group's scan walks
+  uint32_t* floor;    // [kChunkB] ordered score below which no match of the position lies (trajectory)
   void* qrows;        // staged query rows of every layer group (trajectory)
 };
 size_t workspace_bytes_needed(int32_t L, int32_t E, int32_t d_emb, fm_dtype map_dtype);

@@ -172,6 +172,44 @@ __device__ __forceinline__ void split2(const floatx8& v, u16x8& h, u16x8& l) {
 
 
 
+// A query's ranking floor from LDS: the least of its KP parts' best scores or,
+// if larger, the group's shared floor.  The reads are written out, with their
+// own wait: a plain LDS read here makes the compiler wait for every copy into
+// LDS still in flight.
+__device__ __forceinline__ uint32_t lds_address(const void* p) {
+  return static_cast<uint32_t>(reinterpret_cast<uintptr_t>(p));
+}
+template <int KP>
+__device__ __forceinline__ uint32_t read_floor(const uint32_t* part, const uint32_t* group, uint32_t* group_out = nullptr) {
+  static_assert(KP == 1 || KP == 4 || KP == 8, "parts");
+  uint32_t gr, f;
+  if constexpr (KP == 1) {
+    asm volatile("ds_read_b32 %0, %2\n\tds_read_b32 %1, %3\n\ts_waitcnt lgkmcnt(0)"
+                 : "=&v"(gr), "=&v"(f)
+                 : "v"(lds_address(group)), "v"(lds_address(part)));
+  } else {
+    uint32x4 a, b;
+    if constexpr (KP == 4) {
+      asm volatile("ds_read_b32 %0, %2\n\tds_read_b128 %1, %3\n\ts_waitcnt lgkmcnt(0)"
+                   : "=&v"(gr), "=&v"(a)
+                   : "v"(lds_address(group)), "v"(lds_address(part)));
+      b = a;
+    } else {
+      asm volatile("ds_read_b32 %0, %3\n\tds_read_b128 %1, %4\n\tds_read_b128 %2, %4 offset:16\n\ts_waitcnt lgkmcnt(0)"
+                   : "=&v"(gr), "=&v"(a), "=&v"(b)
+                   : "v"(lds_address(group)), "v"(lds_address(part)));
+    }
+    f = a[0];
+#pragma unroll
+    for (int j = 0; j < 4; ++j) {
+      f = a[j] < f ? a[j] : f;
+      f = b[j] < f ? b[j] : f;
+    }
+  }
+  if (group_out != nullptr) *group_out = gr;
+  return gr > f ? gr : f;
+}
+
 // Position of stage j of the scan: slice j / NLG, layer group j % NLG and
 // query ring slot j % NS, stepped from stage to stage without divisions.
 struct StagePos {
@@ -375,6 +413,7 @@ __global__ void __launch_bounds__(256) k_traj_prep(PrepArgs a) {
     a.ws.rq[pos] = real ? rqv : 0.0f;
     a.ws.perm[pos] = real ? b : -1;
     a.ws.sdep[pos] = real ? dc : 0;
+    a.ws.floor[pos] = 0u;
   }
 }
 
@@ -390,7 +429,7 @@ __global__ void __launch_bounds__(256) k_traj_prep(PrepArgs a) {
 // so "stage j has landed" is vmcnt <= the loads of one stage.  Slot (j+2) % 3
 // was last read in stage j-1, which every wave finished before the barrier of
 // stage j, so one barrier per stage suffices.
-template <bool BF, int TQ, int NBA, int KSG, int KTOP, bool DBG>
+template <bool BF, int TQ, int NBA, int KSG, int KTOP, bool DBG, bool FL>
 __global__ void __launch_bounds__(512) k_traj_scan(ScanArgs a) {
   using Raw = typename std::conditional<BF, u16x8, floatx8>::type;
   constexpr int W = 8;                        // waves per workgroup
@@ -407,11 +446,19 @@ __global__ void __launch_bounds__(512) k_traj_scan(ScanArgs a) {
   static_assert(NI < 64, "vmcnt field is 6 bits");
 
   constexpr int SW = W * NBA * 16;            // maps per slice
+  static_assert(KTOP <= W && W % KTOP == 0 && QG <= W * kWave, "parts of the workgroup's maps");
 
   extern __shared__ __align__(16) unsigned char smem[];
   unsigned char* ring = smem;                                              // [NS][Q_STAGE]
   unsigned char* rtab = smem + NS * Q_STAGE;                               // [2][rt_bytes]
-  int32_t* gperm = reinterpret_cast<int32_t*>(rtab + 2 * a.rt_bytes);      // [QG]
+  // ranking floors (ordered scores, see the epilogue): the floor that the
+  // group's workgroups share, and the best score of each of KTOP disjoint
+  // parts of this workgroup's maps per query
+  constexpr int KP = KTOP;
+  constexpr int GF = (QG + 255) / 256 * 256;   // one copy brings 256 floors
+  uint32_t* gfloor = reinterpret_cast<uint32_t*>(rtab + 2 * a.rt_bytes);   // [GF]
+  uint32_t* part = gfloor + GF;                                            // [QG][KP]
+  int32_t* gperm = reinterpret_cast<int32_t*>(part + QG * KP);             // [QG]
   int32_t* gdep = gperm + QG;                                              // [QG]
   float* grq = reinterpret_cast<float*>(gdep + QG);                        // [QG]
   int32_t* gdi = reinterpret_cast<int32_t*>(grq + QG);                     // [QG] distinct-depth index
@@ -588,6 +635,10 @@ __global__ void __launch_bounds__(512) k_traj_scan(ScanArgs a) {
       gdep[r] = a.ws.sdep[pos];
       grq[r] = a.ws.rq[pos];
     }
+    if constexpr (FL) {
+      for (int r = tid; r < QG * KP; r += W * kWave) part[r] = 0u;
+      for (int r = tid; r < GF; r += W * kWave) gfloor[r] = 0u;
+    }
     __syncthreads();
     // Distinct depths of the group (the positions are sorted by depth, deepest
     // first; padding has depth 0): dval[k] is the k-th one, gdi[r] the index of
@@ -624,7 +675,27 @@ __global__ void __launch_bounds__(512) k_traj_scan(ScanArgs a) {
         const_cast<float*>(a.rnorm), static_cast<short>(0),
         static_cast<int>(static_cast<uint32_t>(a.L) * static_cast<uint32_t>(a.rn_stride) * 4u), kBufWord3);
     const int rt_chunks = (nd * SW * 4 + W * 1024 - 1) / (W * 1024);   // 1 KB loads per wave
+    const __amdgpu_buffer_rsrc_t rs_fl = __builtin_amdgcn_make_buffer_rsrc(
+        a.ws.floor + g0, static_cast<short>(0), QG * 4, kBufWord3);
     auto load_rt = [&](int si) {
+      if (FL && si > 0 && (si & (si - 1)) == 0) {
+        // This workgroup's floor goes to the group's (slices before this one
+        // are scored: the stage's barrier has passed), which comes back into
+        // LDS.  Device scope: the group's workgroups run on every XCD.  Before
+        // slices 1, 2, 4, 8, ...: the floor rises with the logarithm of the maps
+        // seen, and a group's workgroups meet at the same few cache lines.
+        if (tid < QG) {
+          uint32_t shared;
+          const uint32_t f = read_floor<KP>(part + tid * KP, gfloor + tid, &shared);
+          uint32_t off = static_cast<uint32_t>(tid) * 4u;
+          asm volatile("" : "+v"(off));   // (a 32-bit offset: the address is not kept in registers)
+          if (f > shared)
+            __hip_atomic_fetch_max(reinterpret_cast<uint32_t*>(reinterpret_cast<char*>(a.ws.floor + g0) + off), f,
+                                   __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        }
+        if (w == 0)
+          __builtin_amdgcn_raw_ptr_buffer_load_lds(rs_fl, (lds_vp)gfloor, 16, lane * 16, 0, 0, 16 /* sc1 */);
+      }
       unsigned char* dst = rtab + (si & 1) * a.rt_bytes;
       const int y_s = 16 * (b_begin + si * (W * NBA));
       for (int i = 0; i < rt_chunks; ++i) {
@@ -785,27 +856,76 @@ __global__ void __launch_bounds__(512) k_traj_scan(ScanArgs a) {
         // End of a slice: cosine = dot * 1/|q[0:p]| * 1/|x[y][0:p]| with the
         // store's prefix inverse norm at the query's depth p; lane (g, c)
         // holds maps 16nb + 4g + i (i = 0..3) of query column c of each tile.
+        //
+        // With FL, a score below its query's floor, a lower bound on the
+        // query's KTOP-th best, takes no part: KTOP disjoint parts of the workgroup's
+        // maps (wavefronts w mod KTOP) each hold a match at least as good as
+        // the least of their best scores, and the group's workgroups share
+        // the largest such bound.  Without it some lane of a wavefront
+        // improves its own list at nearly every score: ranking took half of a
+        // shallow group's time (200,000 Phi-shaped float32 maps, 512 queries,
+        // top-4: 266 -> 205 us with the shares below).  FL serves launches of
+        // two or more query groups; the 256 workgroups of a single group see
+        // too few slices each, and the exchange cost them up to 20%.
 #pragma unroll
         for (int t = 0; t < TQ; ++t) {
           const int r = 16 * t + c;
           const int p = gdep[r];
           const float rq = grq[r];
-          if (p == 0) continue;
           const float* rrow = reinterpret_cast<const float*>(rtab + (si & 1) * a.rt_bytes) + gdi[r] * SW;
+          floatx4 s[NBA];
 #pragma unroll
           for (int nb = 0; nb < NBA; ++nb) {
-            const int y0 = 16 * (blk_wave + nb) + 4 * g;
             const floatx4 rs = *reinterpret_cast<const floatx4*>(rrow + (w * NBA + nb) * 16 + 4 * g);
 #pragma unroll
+            for (int i = 0; i < 4; ++i) s[nb][i] = (BF ? acc[nb][t][i] : acc[nb][t][i] * kDotUnscale) * rq * rs[i];
+          }
+          if constexpr (DBG) {
+            if (p == 0) continue;
+#pragma unroll
+            for (int nb = 0; nb < NBA; ++nb)
+#pragma unroll
+              for (int i = 0; i < 4; ++i) {
+                const int y = 16 * (blk_wave + nb) + 4 * g + i;
+                if (y < y_lo || y >= y_hi) continue;
+                a.dbg[static_cast<int64_t>(gperm[r]) * a.n + y] = s[nb][i];
+              }
+            continue;
+          }
+          float floor_s = __builtin_nanf("");
+          if constexpr (FL) {
+            // (no floor yet, 0, gives a NaN: nothing is below it; a NaN score
+            // is below no floor either, and is looked at where a number is)
+            floor_s = unord_score(read_floor<KP>(part + r * KP, gfloor + r));
+            float top = s[0][0];
+#pragma unroll
+            for (int nb = 0; nb < NBA; ++nb)
+#pragma unroll
+              for (int i = 0; i < 4; ++i) top = fmaxf(top, s[nb][i]);
+            if (__ballot(p != 0 && !(top < floor_s)) == 0) continue;
+          } else if (p == 0) {
+            continue;
+          }
+#pragma unroll
+          for (int nb = 0; nb < NBA; ++nb) {
+#pragma unroll
             for (int i = 0; i < 4; ++i) {
-              const int y = y0 + i;
+              const int y = 16 * (blk_wave + nb) + 4 * g + i;
               // maps outside [y_lo, y_hi) belong to a neighbouring workgroup
-              if (y < y_lo || y >= y_hi) continue;
-              const float dot = BF ? acc[nb][t][i] : acc[nb][t][i] * kDotUnscale;
-              const float s = dot * rq * rs[i];
-              if constexpr (DBG) a.dbg[static_cast<int64_t>(gperm[r]) * a.n + y] = s;
-              best[t].push(make_key(s, y));
+              bool in = y >= y_lo && y < y_hi;
+              if constexpr (FL) in = in && p != 0 && !(s[nb][i] < floor_s);
+              if (in) best[t].push(make_key(s[nb][i], y));
             }
+          }
+          if constexpr (FL) {
+            uint32_t m0 = static_cast<uint32_t>(best[t].v[0] >> 32);
+            uint32_t o = __shfl_xor(m0, 16, kWave);
+            m0 = o > m0 ? o : m0;
+            o = __shfl_xor(m0, 32, kWave);
+            m0 = o > m0 ? o : m0;
+            // (written out, as the floor's reads are)
+            if (g == 0)
+              asm volatile("ds_max_u32 %0, %1" ::"v"(lds_address(part + r * KP + w % KP)), "v"(m0) : "memory");
           }
         }
 #pragma unroll
@@ -842,6 +962,8 @@ __global__ void __launch_bounds__(512) k_traj_scan(ScanArgs a) {
     __syncthreads();
   }
 
+  // the dense form keeps no lists (it serves calls that return no matches)
+  if constexpr (DBG) return;
   // merge the per-lane lists across the 4 lane groups, then across waves
 #pragma unroll
   for (int t = 0; t < TQ; ++t) {
@@ -965,8 +1087,8 @@ int scan_rt_bytes(int TQ, int KSG, int dmax, bool bf) {
 
 // LDS of the scan: 3 ring slots of query planes (8 waves x NI_Q x 1 KB each),
 // two inverse-norm tables, and the group's sorted query info (permutation,
-// depth, 1/|q|, distinct-depth index and values, distinct-depth masks); the
-// top-K merge buffer reuses the ring.
+// depth, 1/|q|, distinct-depth index and values, distinct-depth masks) and
+// ranking floors; the top-K merge buffer reuses the ring.
 size_t scan_lds(bool bf, int TQ, int KSG, int KTOP, int dmax) {
   const int NP = bf ? 1 : 2;
   const int QG = 16 * TQ;
@@ -975,12 +1097,12 @@ size_t scan_lds(bool bf, int TQ, int KSG, int KTOP, int dmax) {
   const size_t merge = static_cast<size_t>(8) * QG * KTOP * 8;
   if (merge > ring) ring = merge;
   return ring + 2 * static_cast<size_t>(scan_rt_bytes(TQ, KSG, dmax, bf)) + static_cast<size_t>(5) * QG * 4 +
-         static_cast<size_t>(8) * ((QG + 63) / 64);
+         static_cast<size_t>(8) * ((QG + 63) / 64) + static_cast<size_t>(4) * (QG * KTOP + (QG + 255) / 256 * 256);
 }
 
-template <bool BF, int TQ, int NBA, int KSG, int KTOP, bool DBG = false>
+template <bool BF, int TQ, int NBA, int KSG, int KTOP, bool DBG, bool FL>
 hipError_t scan_launch(const ScanArgs& a, size_t lds, hipStream_t st) {
-  auto kern = k_traj_scan<BF, TQ, NBA, KSG, KTOP, DBG>;
+  auto kern = k_traj_scan<BF, TQ, NBA, KSG, KTOP, DBG, FL>;
   if (lds > 64 * 1024) {
     const hipError_t err = hipFuncSetAttribute(reinterpret_cast<const void*>(kern),
                                                hipFuncAttributeMaxDynamicSharedMemorySize, static_cast<int>(lds));
@@ -1008,8 +1130,13 @@ constexpr int tq_limit(bool bf, int ksg, int ktop) {
 // NBA (16-map blocks per wave) follows from TQ and KSG (scan_nba).
 template <bool BF, int KSG, int KTOP, int TQ, bool DBG>
 hipError_t scan_tq1(const ScanArgs& a, size_t lds, hipStream_t st) {
-  if constexpr (TQ <= tq_limit(BF, KSG, KTOP))
-    return scan_launch<BF, TQ, scan_nba(TQ, KSG, BF), KSG, KTOP, DBG>(a, lds, st);
+  if constexpr (TQ <= tq_limit(BF, KSG, KTOP)) {
+    // (more than one group: the batch fills the largest group size, unless
+    // LDS holds it down)
+    if constexpr (!DBG && TQ == tq_limit(BF, KSG, KTOP))
+      if (a.n_qg > 1) return scan_launch<BF, TQ, scan_nba(TQ, KSG, BF), KSG, KTOP, false, true>(a, lds, st);
+    return scan_launch<BF, TQ, scan_nba(TQ, KSG, BF), KSG, KTOP, DBG, false>(a, lds, st);
+  }
   return hipErrorInvalidValue;
 }
 
@@ -1124,10 +1251,12 @@ hipError_t launch_match_trajectory(const StoreView& s, const void* q, const int3
     if (G < n_qg) G = n_qg;
     pa.n_qg = n_qg;
     pa.G = G;
-    // slice epilogue vs stage cost, measured on the top-4 Phi-shaped batch:
-    // about 0.16 stage per score kept in a top-4 list, a third of that for
-    // top-1
-    pa.epi16 = TQ * scan_nba(TQ, geo.ksg, bf) * 4 * (KTOP == 1 ? 1 : 3);
+    // slice epilogue vs stage cost in the sharing of the workgroups among the
+    // groups, per query tile and map block: the least total over the
+    // Phi-shaped batches with depths from both laws (weights 0 .. 300 tried:
+    // top-1 154 us at the best against 203 at the worst, top-4 218 .. 271,
+    // top-8 339 .. 520)
+    pa.epi16 = TQ * scan_nba(TQ, geo.ksg, bf) * (KTOP == 1 ? 2 : KTOP == 4 ? 5 : 8);
     const dim3 pgrid(b_pad / 16, nlg + 4);
     if (bf) hipLaunchKernelGGL(k_traj_prep<true>, pgrid, dim3(kThreads), 0, st, pa);
     else hipLaunchKernelGGL(k_traj_prep<false>, pgrid, dim3(kThreads), 0, st, pa);
