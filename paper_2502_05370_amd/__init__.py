@@ -42,7 +42,7 @@ _TORCH = {FM_F32: torch.float32, FM_BF16: torch.bfloat16}
 
 
 def _ptr(t: Optional[torch.Tensor]):
-    return None if t is None else C.c_void_p(t.data_ptr())
+    return None if t is None else t.data_ptr()
 
 
 def _need(t, name: str, dtype, shape, device) -> torch.Tensor:
@@ -50,6 +50,8 @@ def _need(t, name: str, dtype, shape, device) -> torch.Tensor:
     contiguous, of the expected dtype and shape (None in ``shape`` matches any
     size).  The kernels read and write through raw pointers, so a wrong
     layout would be read out of bounds instead of failing; raise instead."""
+    if type(t) is torch.Tensor and t.dtype is dtype and t.shape == shape and t.device == device and t.is_contiguous():
+        return t   # the usual case, in one line: a call checks up to eight tensors
     if t is None:
         raise ValueError(f"{name} is required")
     if not isinstance(t, torch.Tensor):
@@ -70,10 +72,13 @@ def _dev(store: "Store") -> torch.device:
     return store.device
 
 
-def _stream(stream) -> C.c_void_p:
+def _stream(stream) -> int:
+    """The hipStream_t of ``stream``, or of the current stream (read as an
+    integer: building a torch.cuda.Stream for it costs 2.8 us per call, as
+    much as a kernel launch)."""
     if stream is None:
-        stream = torch.cuda.current_stream()
-    return C.c_void_p(stream.cuda_stream)
+        return torch._C._cuda_getCurrentRawStream(torch.cuda.current_device())
+    return stream.cuda_stream
 
 
 def _aligned_bytes(nbytes: int, device) -> torch.Tensor:
@@ -184,7 +189,7 @@ class Store:
             scratch = self._dedup_scratch
         slots = torch.empty(n, dtype=torch.int32, device=self.device)
         _lib.check(_lib.load().fm_store_insert_dedup(self.handle, _ptr(maps), _ptr(embs), n, int(d), _ptr(slots),
-                                                     ws.ptr, ws.nbytes, _ptr(scratch), scratch.numel(),
+                                                     ws.buf.data_ptr(), ws.nbytes, _ptr(scratch), scratch.numel(),
                                                      _stream(stream)), "fm_store_insert_dedup")
         return slots
 
@@ -234,8 +239,8 @@ class TrajPass:
         _need(idx, "out[0] (idx)", torch.int32, (self.B, k), dev)
         _need(score, "out[1] (score)", torch.float32, (self.B, k), dev)
         ws = _ws(self.store, workspace)
-        _lib.check(_lib.load().fm_traj_step(self.store.handle, C.c_void_p(self.buf.data_ptr()), self.nbytes,
-                                            _ptr(q_layer), int(layer), self.B, k, _ptr(idx), _ptr(score), ws.ptr,
+        _lib.check(_lib.load().fm_traj_step(self.store.handle, self.buf.data_ptr(), self.nbytes,
+                                            _ptr(q_layer), int(layer), self.B, k, _ptr(idx), _ptr(score), ws.buf.data_ptr(),
                                             ws.nbytes, _stream(stream)), "fm_traj_step")
         return idx, score
 
@@ -262,7 +267,7 @@ def match_trajectory(store: Store, q: torch.Tensor, depth: torch.Tensor, k: int 
     _need(score, "out[1] (score)", torch.float32, (B, k), dev)
     ws = _ws(store, workspace)
     _lib.check(_lib.load().fm_match_trajectory(store.handle, _ptr(q), _ptr(depth), max_depth, B, k,
-                                               _ptr(idx), _ptr(score), ws.ptr, ws.nbytes, _stream(stream)),
+                                               _ptr(idx), _ptr(score), ws.buf.data_ptr(), ws.nbytes, _stream(stream)),
                "fm_match_trajectory")
     return idx, score
 
@@ -305,7 +310,7 @@ def match_semantic(store: Store, q: torch.Tensor, k: int = 1,
     _need(idx, "out[0] (idx)", torch.int32, (B, k), dev)
     _need(score, "out[1] (score)", torch.float32, (B, k), dev)
     ws = _ws(store, workspace)
-    _lib.check(_lib.load().fm_match_semantic(store.handle, _ptr(q), B, k, _ptr(idx), _ptr(score), ws.ptr,
+    _lib.check(_lib.load().fm_match_semantic(store.handle, _ptr(q), B, k, _ptr(idx), _ptr(score), ws.buf.data_ptr(),
                                              ws.nbytes, _stream(stream)), "fm_match_semantic")
     return idx, score
 
@@ -371,7 +376,7 @@ def match_trajectory_select(store: Store, q: torch.Tensor, depth: torch.Tensor, 
     p = SelectParams(mode, tau, k_min, k_max, blend)
     _lib.check(_lib.load().fm_match_trajectory_select(store.handle, _ptr(q), _ptr(depth), max_depth, B, k,
                                                       _ptr(layer_begin), _ptr(layer_end), C.byref(p), _ptr(idx),
-                                                      _ptr(score), _ptr(mask), _ptr(count), ws.ptr, ws.nbytes,
+                                                      _ptr(score), _ptr(mask), _ptr(count), ws.buf.data_ptr(), ws.nbytes,
                                                       _stream(stream)), "fm_match_trajectory_select")
     return out
 
@@ -391,7 +396,7 @@ def match_semantic_select(store: Store, q: torch.Tensor, layer_begin: torch.Tens
     p = SelectParams(mode, tau, k_min, k_max, blend)
     _lib.check(_lib.load().fm_match_semantic_select(store.handle, _ptr(q), B, k, _ptr(layer_begin),
                                                     _ptr(layer_end), C.byref(p), _ptr(idx), _ptr(score),
-                                                    _ptr(mask), _ptr(count), ws.ptr, ws.nbytes, _stream(stream)),
+                                                    _ptr(mask), _ptr(count), ws.buf.data_ptr(), ws.nbytes, _stream(stream)),
                "fm_match_semantic_select")
     return out
 
@@ -465,5 +470,5 @@ def debug_scores(store: Store, q: Optional[torch.Tensor] = None, depth: Optional
     ws = _ws(store, workspace)
     _lib.check(_lib.load().fm_debug_scores(store.handle, _ptr(q), _ptr(depth),
                                            max_depth if max_depth is not None else store.L, _ptr(q_sem), B,
-                                           _ptr(out), ws.ptr, ws.nbytes, _stream(stream)), "fm_debug_scores")
+                                           _ptr(out), ws.buf.data_ptr(), ws.nbytes, _stream(stream)), "fm_debug_scores")
     return out[:, :n]
