@@ -145,3 +145,30 @@ def test_full_size_pass_sampled():
         assert not rep.failures, (layer, rep.failures[:3])
     # the deepest step recovers the map each query was drawn from
     assert np.mean(out[-1][0][:, 0] == a["src"]) > 0.9
+
+
+@pytest.mark.parametrize("E,B,n,k,dtype", [(8, 17, 1003, 1, "f32"), (16, 65, 333, 4, "bf16"), (17, 33, 65, 1, "bf16"),
+                                           (32, 130, 2051, 8, "f32"), (33, 16, 1, 3, "f32"), (48, 1, 4099, 1, "f32"),
+                                           (64, 1100, 500, 1, "bf16")])
+def test_row_widths_chunks_and_launches(E, B, n, k, dtype):
+    """Rows of one, two and four groups of 16 experts, on and beside their
+    edges; one query, ragged chunks of 64 and more than the 1,024 queries of
+    a launch; stores of one tile, of fewer tiles than a workgroup's register
+    sets and of several tiles per workgroup."""
+    import paper_2502_05370_amd as fm
+    L = 3
+    rng = np.random.default_rng(E + B)
+    maps = rng.dirichlet(np.ones(E), size=(n, L)).astype(np.float32)
+    q = maps[rng.integers(0, n, B)] + rng.uniform(0, 0.02, (B, L, E)).astype(np.float32)
+    if dtype == "bf16":
+        maps, q = synth.bf16_bits(maps), synth.bf16_bits(q)
+    store = fm.Store(n, L, E, 0, dtype)
+    store.insert(to_device(maps, dtype))
+    tp = fm.TrajPass(store, B)
+    rows = np.unique(np.concatenate([[0, B - 1], rng.integers(0, B, 20)]))
+    for l in range(L):
+        idx, score = (x.cpu().numpy() for x in tp.step(to_device(np.ascontiguousarray(q[:, l]), dtype), l, k))
+        rep = compare_depth(maps, dtype, q, l + 1, idx, score, rows)
+        assert not rep.failures, (l, rep.failures[:3])
+        assert np.all(idx[:, 0] >= 0)
+    assert store.check() == 0
