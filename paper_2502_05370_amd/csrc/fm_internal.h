@@ -166,7 +166,7 @@ hipError_t launch_sem_split(const StoreView& s, const SemSplit& p, const uint16_
 // Bc queries takes it, its queries per group, and the scan itself on queries
 // staged by k_traj_prep in its tiled layout (b_pad = groups * queries per
 // group); *R_out receives the partial lists per query for k_finalize.
-bool traj_mm_fits(bool bf, int KTOP, int32_t Bc, int32_t max_depth, int nlg, int ksg);
+bool traj_mm_fits(bool bf, int KTOP, int32_t n, int32_t Bc, int32_t max_depth, int nlg, int ksg);
 int traj_mm_group();
 int traj_mm_workgroups();
 hipError_t launch_traj_mm(const StoreView& s, int spl, int lpg, int ksg, int nlg, int32_t max_depth, int32_t b_pad,

@@ -1181,8 +1181,8 @@ hipError_t launch_match_trajectory(const StoreView& s, const void* q, const int3
   const int nlg = (max_depth + geo.lpg - 1) / geo.lpg;
   for (int b0 = 0; b0 < B; b0 += kChunkB) {
     const int Bc = (B - b0) < kChunkB ? (B - b0) : kChunkB;
-    if (traj_mm_fits(bf, KTOP, Bc, max_depth, nlg, geo.ksg)) {
-      // bf16 top-1 (or dense) batches of more than 128 queries: k_traj_mm
+    if (traj_mm_fits(bf, KTOP, s.n, Bc, max_depth, nlg, geo.ksg)) {
+      // bf16 top-1 (or dense) batches of more than half a band: k_traj_mm
       const int QG = traj_mm_group();
       const int n_qg = (Bc + QG - 1) / QG;
       const int b_pad = n_qg * QG;

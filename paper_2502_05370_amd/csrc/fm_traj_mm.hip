@@ -1,5 +1,5 @@
 // Trajectory-based expert map search (Section 4.2.2, Eq. 5), top-1 form for
-// bfloat16 stores and batches of more than 128 queries.
+// bfloat16 stores and batches of more than 128 queries (96 on larger stores).
 //
 // The batch is the contraction of the depth-sorted query prefixes with the
 // stored maps' prefixes, layer group by layer group, on
@@ -578,13 +578,21 @@ hipError_t traj_mm_launch(const TrajMmArgs& a, hipStream_t st) {
 
 }  // namespace
 
-bool traj_mm_fits(bool bf, int KTOP, int32_t Bc, int32_t max_depth, int nlg, int ksg) {
-  return bf && KTOP == 1 && Bc > 128 && max_depth <= kRows && nlg * ksg >= 2 && (ksg == 1 || ksg == 2);
+int traj_mm_workgroups() { return 256; }
+
+// A band is 256 queries; half a band still pays where each workgroup has a
+// slice and a half or more to walk, since the general scan runs 8 tiles of 128
+// queries at one wavefront row per tile (us, general / this: 200,003 x 24 x 60
+// 100 queries 149.5 / 145.2, 800,000 128 queries 473 / 447, 300,000 x 32 x 8
+// 100 queries 69.4 / 62.3, 100,000 x 32 x 16 120 queries 46.0 / 40.1; but
+// 50,000 x 24 x 60 100 queries 50.7 / 54.4, and 200,003 70 queries 143.0 /
+// 144.8).
+bool traj_mm_fits(bool bf, int KTOP, int32_t n, int32_t Bc, int32_t max_depth, int nlg, int ksg) {
+  const bool wide = Bc > 128 || (Bc > 96 && n >= 16 * kSB * traj_mm_workgroups() * 3 / 2);
+  return bf && KTOP == 1 && wide && max_depth <= kRows && nlg * ksg >= 2 && (ksg == 1 || ksg == 2);
 }
 
 int traj_mm_group() { return kQG; }
-
-int traj_mm_workgroups() { return 256; }
 
 hipError_t launch_traj_mm(const StoreView& s, int spl, int lpg, int ksg, int nlg, int32_t max_depth, int32_t b_pad,
                           const Workspace& ws, float* dbg, int32_t* R_out, hipStream_t st) {

@@ -132,3 +132,17 @@ def test_traj_mm_signed_and_scaled_queries():
     rep = compare_match(s, a, g.idx, g.score, oi, os_, np.arange(s.B))
     assert not rep.failures, rep.failures[:5]
     assert np.all(g.score[0::3, 0] <= 0.0)
+
+
+@pytest.mark.parametrize("B", [96, 97, 128])
+def test_traj_mm_half_a_band(B):
+    """Batches on both sides of half a band, on a store of one and a half
+    slices per workgroup or more."""
+    s = _bf16_spec(1, 8, 3, 98305 + 7, B, 3)
+    a = synth.generate(s)
+    g = run_gpu(s, a, max_depth=3)
+    assert g.flags == 0
+    rows = np.unique(np.concatenate([[0, 1, B - 1], np.arange(2, B, 9)]))
+    oi, os_ = oracle_match(s, a, rows)
+    rep = compare_match(s, a, g.idx, g.score, oi, os_, rows)
+    assert not rep.failures, rep.failures[:5]
