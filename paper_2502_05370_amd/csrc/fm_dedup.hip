@@ -35,25 +35,22 @@ struct RdyArgs {
   int32_t size;        // stored iterations y in [0, size)
   int32_t m;           // new iterations (rows)
   int32_t R;           // chunks per row
-  int32_t per;         // y per chunk, a multiple of 256 * kUnroll
+  int32_t per;         // y per chunk
   uint64_t* partial;   // [m][R][kCand] packed keys
 };
 
-constexpr int kUnroll = 8;   // RDY values loaded per thread before they are ranked (sort8_desc)
+constexpr int kUnroll = 8;     // RDY values ranked together (sort8_desc)
+constexpr int kHeld = 64;      // RDY values a thread holds: a chunk of 256 * kHeld
+constexpr int kShort = 256;    // candidates of a chunk that are ranked by counting
 
-__global__ void __launch_bounds__(256) k_rdy_partial(RdyArgs a) {
-  __shared__ uint64_t lists[256 / kWave][kCand];
-  const int r = blockIdx.y;
-  const int rr = blockIdx.x;
+// The 8 best of a chunk by per-thread lists: batches of 8 values sorted by a
+// network and merged into the thread's list, then the lists merged.
+__device__ void rdy_partial_lists(const RdyArgs& a, const float* row, int lo, int hi, uint64_t* out,
+                                  uint64_t (*lists)[kCand]) {
   const int lane = threadIdx.x % kWave;
   const int w = threadIdx.x / kWave;
-  const int lo = rr * a.per;
-  const int hi = lo + a.per < a.size ? lo + a.per : a.size;
-  const float* row = a.rdy + static_cast<int64_t>(r) * a.size;
   TopK<kCand> t;
   t.clear();
-  // batches of 8 values per thread: loaded together, sorted by a network and
-  // merged into the thread's list
   for (int y0 = lo + static_cast<int>(threadIdx.x); y0 < hi; y0 += 256 * kUnroll) {
     float v[kUnroll];
 #pragma unroll
@@ -88,9 +85,77 @@ __global__ void __launch_bounds__(256) k_rdy_partial(RdyArgs a) {
     b.clear();
 #pragma unroll
     for (int ww = 0; ww < 256 / kWave; ++ww) b.merge(lists[ww]);
-    uint64_t* out = a.partial + (static_cast<int64_t>(r) * a.R + rr) * kCand;
 #pragma unroll
     for (int j = 0; j < kCand; ++j) out[j] = b.v[j];
+  }
+}
+
+// The 8 best of each chunk of a row.  A thread holds its 64 values; the least
+// of the best values of the chunk's 8 half-wavefronts is a floor that the 8
+// best reach, and the few values at or above it (about 25 of 16,384) are
+// collected in LDS and placed by counting.  A chunk with more of them than
+// kShort (rows of equal or NaN values), or longer than the threads hold, goes
+// through per-thread lists, which every chunk did before: 256 x 100,000 values
+// 51 us, bound by the sorting networks' vector instructions.
+__global__ void __launch_bounds__(256) k_rdy_partial(RdyArgs a) {
+  __shared__ uint64_t lists[256 / kWave][kCand];
+  __shared__ uint64_t cand[kShort];
+  __shared__ uint32_t half_best[kCand];
+  __shared__ int32_t n_cand;
+  static_assert(256 / 32 == kCand, "a half-wavefront per candidate");
+  const int tid = threadIdx.x;
+  const int r = blockIdx.y;
+  const int rr = blockIdx.x;
+  const int lo = rr * a.per;
+  const int hi = lo + a.per < a.size ? lo + a.per : a.size;
+  const float* row = a.rdy + static_cast<int64_t>(r) * a.size;
+  uint64_t* out = a.partial + (static_cast<int64_t>(r) * a.R + rr) * kCand;
+  if (a.per > 256 * kHeld) {
+    rdy_partial_lists(a, row, lo, hi, out, lists);
+    return;
+  }
+  uint32_t o[kHeld];   // ordered values (0: NaN, or no entry)
+  {
+    float v[kHeld];
+#pragma unroll
+    for (int u = 0; u < kHeld; ++u) v[u] = lo + tid + 256 * u < hi ? row[lo + tid + 256 * u] : __builtin_nanf("");
+#pragma unroll
+    for (int u = 0; u < kHeld; ++u) o[u] = ord_score(v[u]);
+  }
+  uint32_t best = o[0];
+#pragma unroll
+  for (int u = 1; u < kHeld; ++u) best = o[u] > best ? o[u] : best;
+#pragma unroll
+  for (int m = 1; m < 32; m <<= 1) {
+    const uint32_t x = __shfl_xor(best, m, kWave);
+    best = x > best ? x : best;
+  }
+  if (tid % 32 == 0) half_best[tid / 32] = best;
+  if (tid == 0) n_cand = 0;
+  __syncthreads();
+  uint32_t floor = half_best[0];
+#pragma unroll
+  for (int j = 1; j < kCand; ++j) floor = half_best[j] < floor ? half_best[j] : floor;
+#pragma unroll
+  for (int u = 0; u < kHeld; ++u) {
+    const int y = lo + tid + 256 * u;
+    if (o[u] >= floor && y < hi) {
+      const int at = atomicAdd(&n_cand, 1);
+      if (at < kShort) cand[at] = (static_cast<uint64_t>(o[u]) << 32) | static_cast<uint32_t>(~static_cast<uint32_t>(y));
+    }
+  }
+  __syncthreads();
+  const int N = n_cand;
+  if (N > kShort) {
+    rdy_partial_lists(a, row, lo, hi, out, lists);
+    return;
+  }
+  if (tid >= N && tid < kCand) out[tid] = 0ull;   // fewer than 8 entries
+  if (tid < N) {
+    const uint64_t mine = cand[tid];
+    int rank = 0;
+    for (int i = 0; i < N; ++i) rank += cand[i] > mine ? 1 : 0;
+    if (rank < kCand) out[rank] = mine;
   }
 }
 

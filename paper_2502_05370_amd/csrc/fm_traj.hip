@@ -104,6 +104,7 @@ struct ScanArgs {
   int32_t rt_bytes;   // LDS bytes of one inverse-norm table (whole 8 KB chunks)
   Workspace ws;
   float* dbg;         // optional dense scores [B][n]
+  int32_t vec16;      // dense rows written 16 bytes at a time: n % 4 == 0, an aligned buffer
 };
 
 // Stable sort of the batch by depth, deepest first.  A query's position is
@@ -883,13 +884,18 @@ __global__ void __launch_bounds__(512) k_traj_scan(ScanArgs a) {
           if constexpr (DBG) {
             if (p == 0) continue;
 #pragma unroll
-            for (int nb = 0; nb < NBA; ++nb)
-#pragma unroll
-              for (int i = 0; i < 4; ++i) {
-                const int y = 16 * (blk_wave + nb) + 4 * g + i;
-                if (y < y_lo || y >= y_hi) continue;
-                a.dbg[static_cast<int64_t>(gperm[r]) * a.n + y] = s[nb][i];
+            for (int nb = 0; nb < NBA; ++nb) {
+              // the lane's 4 maps as one 16-byte store where the row allows it
+              const int y0 = 16 * (blk_wave + nb) + 4 * g;
+              float* out = a.dbg + static_cast<int64_t>(gperm[r]) * a.n + y0;
+              if (a.vec16 != 0 && y0 >= y_lo && y0 + 3 < y_hi) {
+                *reinterpret_cast<floatx4*>(out) = s[nb];
+                continue;
               }
+#pragma unroll
+              for (int i = 0; i < 4; ++i)
+                if (y0 + i >= y_lo && y0 + i < y_hi) out[i] = s[nb][i];
+            }
             continue;
           }
           float floor_s = __builtin_nanf("");
@@ -1288,6 +1294,7 @@ hipError_t launch_match_trajectory(const StoreView& s, const void* q, const int3
     a.rt_bytes = scan_rt_bytes(TQ, geo.ksg, max_depth, bf);
     a.ws = ws;
     a.dbg = dbg_scores != nullptr ? dbg_scores + static_cast<int64_t>(b0) * s.n : nullptr;
+    a.vec16 = s.n % 4 == 0 && reinterpret_cast<uintptr_t>(a.dbg) % 16 == 0;
     if (dbg_scores != nullptr) {
       // same arithmetic as the match kernels, plus the dense score stores
       err = bf ? scan_ksg<true, 1, true>(geo.ksg, TQ, a, lds, st) : scan_ksg<false, 1, true>(geo.ksg, TQ, a, lds, st);

@@ -174,3 +174,29 @@ def test_invalid_arguments_enqueue_nothing():
         store.insert_dedup(big, None, 0)
     assert store.size == 16
     _check_contents(s, store, a["maps"], None, a["maps"][:2], None)
+
+
+@pytest.mark.parametrize("n", [3, 255, 600, 16384, 16388, 40001])
+def test_equal_and_nan_redundancies(n):
+    """Rows whose best candidates cannot be told apart: every stored map the
+    same (all values tie, the lowest free indices are taken in order, past the
+    8 kept candidates), and NaN maps (ranked last), on both sides of a chunk of
+    16,384 values and of the candidates ranked by counting."""
+    import paper_2502_05370_amd as fm
+    L, E, m = 2, 8, 12
+    rng = np.random.default_rng(n)
+    one = rng.dirichlet(np.ones(E), size=L).astype(np.float32)
+    maps = np.repeat(one[None], n, axis=0)
+    maps[n // 2:, 0, 1] = np.nan            # the later half scores NaN
+    store = fm.Store(n, L, E, 0, "f32")
+    store.insert(to_device(maps, "f32"))
+    new = np.repeat(one[None], min(m, n), axis=0)
+    slots = store.insert_dedup(to_device(new, "f32"), None, 0).cpu().numpy()
+    assert list(slots) == list(range(len(new))), slots
+    # distinct maps with a few planted copies: each copy's original is taken
+    maps = rng.dirichlet(np.ones(E), size=(n, L)).astype(np.float32)
+    pick = rng.permutation(n)[:min(m, n)]
+    store = fm.Store(n, L, E, 0, "f32")
+    store.insert(to_device(maps, "f32"))
+    slots = store.insert_dedup(to_device(maps[pick], "f32"), None, 0).cpu().numpy()
+    assert list(slots) == list(pick), (slots, pick)
