@@ -163,6 +163,35 @@ struct TopK {
   }
 };
 
+// Dense semantic output of one query's 4 consecutive maps y0 .. y0+3 at o (the
+// row's element of map y0): the cosines v, or w_self * v + w_mix * mix with a
+// second dense matrix (float64, rounded once); one 16-byte access each where
+// `whole`, else the maps below n.
+__device__ __forceinline__ void store_dense4(float* out, const float* mix, double w_self, double w_mix, bool whole,
+                                             int64_t o, int y0, int n, floatx4 v) {
+  if (mix != nullptr) {
+    floatx4 mv = floatx4{0.f, 0.f, 0.f, 0.f};
+    if (whole) {
+      mv = *reinterpret_cast<const floatx4*>(mix + o);
+    } else {
+#pragma unroll
+      for (int r = 0; r < 4; ++r)
+        if (y0 + r < n) mv[r] = mix[o + r];
+    }
+#pragma unroll
+    for (int r = 0; r < 4; ++r)
+      v[r] = static_cast<float>(__dadd_rn(__dmul_rn(w_self, static_cast<double>(v[r])),
+                                          __dmul_rn(w_mix, static_cast<double>(mv[r]))));
+  }
+  if (whole) {
+    *reinterpret_cast<floatx4*>(out + o) = v;
+  } else {
+#pragma unroll
+    for (int r = 0; r < 4; ++r)
+      if (y0 + r < n) out[o + r] = v[r];
+  }
+}
+
 // Sort 8 keys descending in place (19-comparator network).
 __device__ __forceinline__ void sort8_desc(uint64_t* x) {
   constexpr int kNet[19][2] = {{0, 2}, {1, 3}, {4, 6}, {5, 7}, {0, 4}, {1, 5}, {2, 6}, {3, 7}, {0, 1}, {2, 3},

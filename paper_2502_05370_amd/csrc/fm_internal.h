@@ -159,9 +159,11 @@ struct SemSplit {
   int group = 0;      // queries per group
   int R = 0;          // partial lists per query
 };
-SemSplit sem_split_plan(int32_t Bc, int32_t n, int32_t d, int KTOP);
+SemSplit sem_split_plan(int32_t Bc, int32_t n, int32_t d, int KTOP, bool dense);
+// (dbg, mix, w_self, w_mix: the dense form, as for launch_sem_mm.)
 hipError_t launch_sem_split(const StoreView& s, const SemSplit& p, const uint16_t* q, int32_t Bc, int KTOP,
-                            const Workspace& ws, hipStream_t st);
+                            const Workspace& ws, hipStream_t st, float* dbg = nullptr, const float* mix = nullptr,
+                            double w_self = 1.0, double w_mix = 0.0);
 // Top-1 trajectory scan of bf16 stores (fm_traj_mm.hip): whether a chunk of
 // Bc queries takes it, its queries per group, and the scan itself on queries
 // staged by k_traj_prep in its tiled layout (b_pad = groups * queries per

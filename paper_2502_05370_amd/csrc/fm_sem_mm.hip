@@ -286,27 +286,7 @@ __global__ void __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(2, 2))
               floatx4 v;
 #pragma unroll
               for (int r = 0; r < 4; ++r) v[r] = acc[i][t][r] * rqb * rx[r];
-              if (a.mix != nullptr) {
-                floatx4 mv = floatx4{0.f, 0.f, 0.f, 0.f};
-                if (whole) {
-                  mv = *reinterpret_cast<const floatx4*>(a.mix + o);
-                } else {
-#pragma unroll
-                  for (int r = 0; r < 4; ++r)
-                    if (y0 + r < a.n) mv[r] = a.mix[o + r];
-                }
-#pragma unroll
-                for (int r = 0; r < 4; ++r)
-                  v[r] = static_cast<float>(__dadd_rn(__dmul_rn(a.w_self, static_cast<double>(v[r])),
-                                                      __dmul_rn(a.w_mix, static_cast<double>(mv[r]))));
-              }
-              if (whole) {
-                *reinterpret_cast<floatx4*>(a.dbg + o) = v;
-              } else {
-#pragma unroll
-                for (int r = 0; r < 4; ++r)
-                  if (y0 + r < a.n) a.dbg[o + r] = v[r];
-              }
+              store_dense4(a.dbg, a.mix, a.w_self, a.w_mix, whole, o, y0, a.n, v);
             }
             continue;
           }

@@ -16,6 +16,9 @@
 // each (block, query tile) pair by one wavefront, which scales the sums by
 // 1/|x| and keeps its query tile's best in per-lane top-K lists.
 //
+// The dense form writes every cosine, or its weighted sum with a second
+// dense matrix (the deduplicating insert's RDY), instead of keeping lists.
+//
 // A list ranks by dot * 1/|x|: the query's factor 1/|q| is positive (or 0 for
 // a zero query, whose dots are all 0) and is applied by the merge.
 //
@@ -49,6 +52,11 @@ struct SplitArgs {
   const uint16_t* q;     // RAW: [B][d] rows; else staged tiles
   float* rq;             // [b_pad] 1/|q| (RAW: written here)
   uint64_t* partial;     // [b_pad][R][KTOP]
+  // dense form: the scores [B][n], or w_self * score + w_mix * mix
+  float* dbg;
+  const float* mix;
+  double w_self, w_mix;
+  int32_t vec16;         // dense rows written (and mix read) 16 bytes at a time: n % 4 == 0, aligned buffers
   int32_t n, d, ksteps, B;
   int32_t n_qg;          // query groups
   int32_t R;             // workgroups per query group
@@ -75,7 +83,7 @@ __device__ __forceinline__ uint64_t split_key(float s, int32_t idx) {
 
 }  // namespace
 
-template <int W, int NB, int TQ, int D, int KTOP, bool RAW>
+template <int W, int NB, int TQ, int D, int KTOP, bool RAW, bool DENSE>
 __global__ void __launch_bounds__(W * 64) __attribute__((amdgpu_waves_per_eu(W / 4, W / 4))) k_sem_split(SplitArgs a) {
   using S = SplitShape<W, NB, TQ>;
   constexpr int TC = S::TC, PAIRS = S::PAIRS, PH = S::PH;
@@ -261,10 +269,23 @@ __global__ void __launch_bounds__(W * 64) __attribute__((amdgpu_waves_per_eu(W /
           float xn[4];
 #pragma unroll
           for (int r = 0; r < 4; ++r) xn[r] = y0 + r < a.n ? a.xnorm[y0 + r] : 0.0f;
+          float rx[4];
 #pragma unroll
-          for (int r = 0; r < 4; ++r) {
-            const float rx = xn[r] > 0.0f ? __builtin_amdgcn_rcpf(xn[r]) : (xn[r] != xn[r] ? xn[r] : 0.0f);
-            if (y0 + r < a.n) best[ph].push(split_key(sum[r] * rx, y0 + r));
+          for (int r = 0; r < 4; ++r) rx[r] = xn[r] > 0.0f ? __builtin_amdgcn_rcpf(xn[r]) : (xn[r] != xn[r] ? xn[r] : 0.0f);
+          if constexpr (DENSE) {
+            const int b = g0 + 16 * (ph * TC + tt) + c;
+            if (b < a.B) {
+              const float rq = a.rq[b];
+              floatx4 v;
+#pragma unroll
+              for (int r = 0; r < 4; ++r) v[r] = sum[r] * rq * rx[r];
+              store_dense4(a.dbg, a.mix, a.w_self, a.w_mix, a.vec16 != 0 && y0 + 3 < a.n,
+                           static_cast<int64_t>(b) * a.n + y0, y0, a.n, v);
+            }
+          } else {
+#pragma unroll
+            for (int r = 0; r < 4; ++r)
+              if (y0 + r < a.n) best[ph].push(split_key(sum[r] * rx[r], y0 + r));
           }
         }
       }
@@ -276,6 +297,8 @@ __global__ void __launch_bounds__(W * 64) __attribute__((amdgpu_waves_per_eu(W /
 #pragma unroll
       for (int t = 0; t < TQ; ++t) acc[i][t] = floatx4{0.f, 0.f, 0.f, 0.f};
   }
+
+  if constexpr (DENSE) return;   // no lists
 
   // merge: the four lane groups of a query, then the W / TC wavefronts of its tile
   uint64_t* mbuf = reinterpret_cast<uint64_t*>(smem);   // [W][PH][16][KTOP]
@@ -309,14 +332,15 @@ __global__ void __launch_bounds__(W * 64) __attribute__((amdgpu_waves_per_eu(W /
 
 namespace {
 
-template <int W, int NB, int TQ, int D, int KTOP, bool RAW>
+template <int W, int NB, int TQ, int D, int KTOP, bool RAW, bool DENSE = false>
 hipError_t split_launch(const SplitArgs& a, hipStream_t st) {
   using S = SplitShape<W, NB, TQ>;
   constexpr size_t red = static_cast<size_t>(W) * S::PAIRS * 1024;
   constexpr size_t mrg = static_cast<size_t>(W) * S::PH * 16 * KTOP * 8;
   constexpr size_t lds = red > mrg ? red : mrg;
   static_assert(lds <= 160 * 1024, "LDS");
-  auto kern = k_sem_split<W, NB, TQ, D, KTOP, RAW>;
+  static_assert(!(RAW && DENSE), "the dense form reads 1/|q| in the scan");
+  auto kern = k_sem_split<W, NB, TQ, D, KTOP, RAW, DENSE>;
   if (lds > 64 * 1024) {
     const hipError_t err = hipFuncSetAttribute(reinterpret_cast<const void*>(kern),
                                                hipFuncAttributeMaxDynamicSharedMemorySize, static_cast<int>(lds));
@@ -382,7 +406,7 @@ constexpr double kMmRate = 5.8e6;
 // queries 24.6 against 93; 16,000 of d = 2048, 8 queries 13 against 51, 100
 // queries 25.7 against 51, 1,000 queries 120 against 58.7; 60,000 of d = 2048,
 // 30 queries 50 against 59, 128 queries 82 against 60.
-SemSplit sem_split_plan(int32_t Bc, int32_t n, int32_t d, int KTOP) {
+SemSplit sem_split_plan(int32_t Bc, int32_t n, int32_t d, int KTOP, bool dense) {
   const int n_blocks = (n + 15) / 16;
   const int ksteps = d / 32;
   const double bytes = 2.0 * n * d;
@@ -398,6 +422,7 @@ SemSplit sem_split_plan(int32_t Bc, int32_t n, int32_t d, int KTOP) {
   for (int i = 0; i < static_cast<int>(sizeof(kShapes) / sizeof(kShapes[0])); ++i) {
     const ShapeInfo& si = kShapes[i];
     const int n_qg = (Bc + 16 * si.tq - 1) / (16 * si.tq);
+    if (dense && si.raw) continue;
     if (si.tq == 8 && KTOP == 8) continue;   // its lists do not fit the registers (19 spilled, 72 -> 95 us)
     const int R = split_workgroups(n_qg, n_blocks, si.nb);
     const double steps = ((n_blocks + R - 1) / R + si.nb - 1) / si.nb;
@@ -416,8 +441,14 @@ SemSplit sem_split_plan(int32_t Bc, int32_t n, int32_t d, int KTOP) {
 }
 
 hipError_t launch_sem_split(const StoreView& s, const SemSplit& p, const uint16_t* q, int32_t Bc, int KTOP,
-                            const Workspace& ws, hipStream_t st) {
+                            const Workspace& ws, hipStream_t st, float* dbg, const float* mix, double w_self,
+                           double w_mix) {
   SplitArgs a;
+  a.dbg = dbg;
+  a.mix = mix;
+  a.w_self = w_self;
+  a.w_mix = w_mix;
+  a.vec16 = s.n % 4 == 0 && reinterpret_cast<uintptr_t>(dbg) % 16 == 0 && reinterpret_cast<uintptr_t>(mix) % 16 == 0;
   a.x = s.embs;
   a.xnorm = s.emb_norm;
   a.q = p.raw ? q : static_cast<const uint16_t*>(ws.qrows);
@@ -431,6 +462,11 @@ hipError_t launch_sem_split(const StoreView& s, const SemSplit& p, const uint16_
   a.R = p.R;
   a.n_blocks = (s.n + 15) / 16;
   a.grid = (a.n_qg * a.R + 7) / 8 * 8;
+  if (dbg != nullptr) {
+    if (p.shape == 3) return split_launch<8, 4, 4, 2, 1, false, true>(a, st);
+    if (p.shape == 4) return split_launch<8, 4, 8, 2, 1, false, true>(a, st);
+    return hipErrorInvalidValue;
+  }
   if (KTOP == 1) return split_shape<1>(p.shape, a, st);
   if (KTOP == 4) return split_shape<4>(p.shape, a, st);
   return split_shape<8>(p.shape, a, st);

@@ -9,7 +9,7 @@ import pytest
 
 import oracle
 import synth
-from parity import compare_topk, to_device
+from parity import SCORE_TOL, compare_topk, to_device
 
 pytestmark = pytest.mark.gpu
 
@@ -57,3 +57,9 @@ def test_split_scan_matches_oracle(n, d, B):
         for b in set(range(B)) - set(finite):
             assert list(idx[b, :m]) == list(range(m)) and np.isnan(score[b, :m]).all()
             assert (idx[b, m:] == -1).all()
+    # the dense form: every cosine
+    dense = fm.debug_scores(store, q_sem=to_device(q, "bf16")).cpu().numpy()
+    for b in finite[:40]:
+        ref = oracle.semantic_scores(e64, q64[b])
+        assert np.array_equal(np.isnan(ref), np.isnan(dense[b]))
+        assert np.nanmax(np.abs(dense[b] - ref)) <= SCORE_TOL
