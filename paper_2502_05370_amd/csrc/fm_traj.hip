@@ -12,7 +12,9 @@
 //                   bf16 stores), zero beyond each query's depth, so the scan
 //                   copies them verbatim; it also shares the scan's
 //                   workgroups among the query groups by their cost.
-//  k_traj_scan      workgroup = one group of 16*TQ sorted queries x an even
+//  k_traj_scan      (small stores and batches: fm_traj_split.hip; large bf16
+//                   top-1 batches: fm_traj_mm.hip)
+//                   workgroup = one group of 16*TQ sorted queries x an even
 //                   share of the store (to the map) among the group's
 //                   workgroups, walked as slices of 8 waves x NBA 16-map
 //                   blocks.  The map quads of a stage two stages ahead load
@@ -42,6 +44,7 @@
 
 #include "fm_device.h"
 #include "fm_internal.h"
+#include "fm_traj_geo.h"
 
 namespace fm {
 
@@ -49,29 +52,6 @@ namespace {
 
 constexpr int kThreads = 256;
 constexpr int kWaves = kThreads / kWave;
-
-typedef float floatx8 __attribute__((ext_vector_type(8)));
-typedef uint16_t u16x4 __attribute__((ext_vector_type(4)));
-typedef _Float16 half2v __attribute__((ext_vector_type(2)));
-typedef float float2v __attribute__((ext_vector_type(2)));
-
-
-// Slot geometry of a store (host-computed).
-struct Geo {
-  int32_t spl;   // slots per layer: E when LPG > 1, else E rounded up to 32
-  int32_t lpg;   // layers per layer group
-  int32_t ksg;   // 32-slot k-steps per layer group
-};
-
-// Bytes of one staged query plane row: 32*ksg 16-bit slots, in 16-byte
-// units.  With ksg > 1 unit u of row r is stored at unit u ^ (r & 7) of the
-// row, so the 16 rows a wave reads at one logical unit spread over 8 distinct
-// 16-byte bank groups (with ksg = 1 a wave's read of 16 rows is one
-// contiguous 1 KB already).
-__host__ __device__ __forceinline__ int qrow_bytes(int ksg) { return 64 * ksg; }
-__host__ __device__ __forceinline__ int qrow_unit(int ksg, int row, int unit) {
-  return ksg > 1 ? unit ^ (row & 7) : unit;
-}
 
 struct PrepArgs {
   const void* q;
@@ -146,32 +126,6 @@ __device__ __forceinline__ int position_of(int b, int dc, const unsigned long lo
   r += __popcll(row[wd] & ((1ull << (b % 64)) - 1ull));
   return start[dc - 1] + r;
 }
-
-// float32 -> two float16 parts (bit patterns) of A = 2^12 a: hi = RN16(A),
-// lo = RN16(A - hi).  A - hi is exact in float32 (one fused multiply-add of
-// the widened hi); hi is finite for |a| < 16 (values above 8 are flagged
-// where they enter).  Pairs convert with one packed conversion each.
-constexpr float kSplitScale = 4096.0f;                        // 2^12
-constexpr float kDotUnscale = 1.0f / (4096.0f * 4096.0f);     // 2^-24
-constexpr float kRangeLimit = 8.0f;
-__device__ __forceinline__ void split2(const floatx8& v, u16x8& h, u16x8& l) {
-  uint32x4 hw, lw;
-#pragma unroll
-  for (int j = 0; j < 4; ++j) {
-    const float2v x = {v[2 * j] * kSplitScale, v[2 * j + 1] * kSplitScale};
-    const half2v hb = __builtin_convertvector(x, half2v);
-    float2v r;
-    r[0] = __builtin_fmaf(static_cast<float>(hb[0]), -1.0f, x[0]);
-    r[1] = __builtin_fmaf(static_cast<float>(hb[1]), -1.0f, x[1]);
-    const half2v lb = __builtin_convertvector(r, half2v);
-    hw[j] = __builtin_bit_cast(uint32_t, hb);
-    lw[j] = __builtin_bit_cast(uint32_t, lb);
-  }
-  h = __builtin_bit_cast(u16x8, hw);
-  l = __builtin_bit_cast(u16x8, lw);
-}
-
-
 
 // A query's ranking floor from LDS: the least of its KP parts' best scores or,
 // if larger, the group's shared floor.  The reads are written out, with their
@@ -1061,20 +1015,6 @@ hipError_t launch_finalize(const uint64_t* partial, const int32_t* perm, int32_t
 
 namespace {
 
-Geo geometry(int E) {
-  Geo g;
-  if (E >= 8 && 32 % E == 0) {
-    g.spl = E;
-    g.lpg = 32 / E;
-    g.ksg = 1;
-  } else {
-    g.spl = (E + 31) / 32 * 32;
-    g.lpg = 1;
-    g.ksg = g.spl / 32;
-  }
-  return g;
-}
-
 // 16-map blocks per wave (NBA): two, unless the query group is large; groups
 // of 8 query tiles keep two when one k-step covers a layer group or the store
 // is bf16 (their accumulators and operands still fit the registers).  Two
@@ -1187,7 +1127,16 @@ hipError_t launch_match_trajectory(const StoreView& s, const void* q, const int3
   const int nlg = (max_depth + geo.lpg - 1) / geo.lpg;
   for (int b0 = 0; b0 < B; b0 += kChunkB) {
     const int Bc = (B - b0) < kChunkB ? (B - b0) : kChunkB;
-    if (traj_mm_fits(bf, KTOP, s.n, Bc, max_depth, nlg, geo.ksg)) {
+    int TQ = 1;
+    while (16 * TQ < Bc && TQ < tq_max) TQ *= 2;
+    // smaller query groups when the staged planes of one would not fit the ring
+    while (TQ > 1 && scan_lds(bf, TQ, geo.ksg, KTOP, max_depth) > kLds) TQ /= 2;
+    // the split-depth scan where it is the faster one (fm_traj_split.hip; it
+    // has no dense form)
+    const bool mm = traj_mm_fits(bf, KTOP, s.n, Bc, max_depth, nlg, geo.ksg);
+    TrajSplit sp;
+    if (dbg_scores == nullptr) sp = traj_split_plan(s, geo, Bc, nlg, TQ, scan_nba(TQ, geo.ksg, bf), mm);
+    if (mm && sp.shape < 0) {
       // bf16 top-1 (or dense) batches of more than half a band: k_traj_mm
       const int QG = traj_mm_group();
       const int n_qg = (Bc + QG - 1) / QG;
@@ -1229,11 +1178,7 @@ hipError_t launch_match_trajectory(const StoreView& s, const void* q, const int3
       }
       continue;
     }
-    int TQ = 1;
-    while (16 * TQ < Bc && TQ < tq_max) TQ *= 2;
-    // smaller query groups when the staged planes of one would not fit the ring
-    while (TQ > 1 && scan_lds(bf, TQ, geo.ksg, KTOP, max_depth) > kLds) TQ /= 2;
-    const int QG = 16 * TQ;
+    const int QG = sp.shape >= 0 ? sp.group : 16 * TQ;
     const int n_qg = (Bc + QG - 1) / QG;
     const int b_pad = n_qg * QG;
 
@@ -1268,6 +1213,19 @@ hipError_t launch_match_trajectory(const StoreView& s, const void* q, const int3
     else hipLaunchKernelGGL(k_traj_prep<false>, pgrid, dim3(kThreads), 0, st, pa);
     hipError_t err = hipGetLastError();
     if (err != hipSuccess) return err;
+
+    if (sp.shape >= 0) {
+      err = launch_traj_split(s, sp, geo, Bc, b_pad, KTOP, ws, st);
+      if (err != hipSuccess) return err;
+      err = fuse != nullptr
+                ? launch_merge_select(s, ws.partial, ws.perm, Bc, sp.R, k, KTOP, nullptr, 0,
+                                      idx_out + static_cast<int64_t>(b0) * k, score_out + static_cast<int64_t>(b0) * k,
+                                      fuse->at(b0, s.L), st)
+                : launch_finalize(ws.partial, ws.perm, Bc, sp.R, k, KTOP, idx_out + static_cast<int64_t>(b0) * k,
+                                  score_out + static_cast<int64_t>(b0) * k, st);
+      if (err != hipSuccess) return err;
+      continue;
+    }
 
     const size_t lds = scan_lds(bf, TQ, geo.ksg, KTOP, max_depth);
     if (lds > kLds) return hipErrorInvalidConfiguration;
