@@ -64,10 +64,8 @@ COPY_BYTES_KIB = 262144.0
 COPY_COUNTERS_KIB = {"FETCH_SIZE": 131083.5, "WRITE_SIZE": 262144.0}
 COUNTERS_KIB = {
     # workload: {kernel: (FETCH_SIZE KiB, WRITE_SIZE KiB) per dispatch}
-    "mixtral_traj_n1k": {"k_traj_scan": (610.1, 10.9)},
     "qwen_traj_n50k_b64": {"k_traj_scan": (138797.4, 128.0)},
     "semantic_d4096_n100k_b256": {"k_sem_mm": (417145.2, 512.0)},
-    "phi_traj_top4_n200k_b512": {"k_traj_scan": (333131.3, 1012.0)},
     "qwen_mixed_bf16_n1m_b1024": {"k_sem_mm": (2657013.4, 512.0), "k_traj_mm": (2276903.6, 557.0)},
 }
 
@@ -83,15 +81,19 @@ def counter_traffic(workload, kernel):
 
 
 def scan_kernels(s):
-    """The scan kernel the library launches for each half of workload s's
-    batch (the same rules as the library's dispatch): the semantic top-1
-    scan k_sem_mm for k = 1, else k_sem_scan; the bf16 top-1 trajectory scan
-    k_traj_mm for bf16 stores, k = 1 and more than 128 queries per launch,
-    else k_traj_scan."""
-    sem = ("k_sem_mm" if s.k == 1 else "k_sem_scan") if s.B_sem else None
+    """The scan kernel the library launches for each half of full-size workload
+    s's batch: the split-k and split-depth scans for a store of a few thousand
+    entries; else the semantic top-1 scan k_sem_mm for k = 1, k_sem_scan for
+    more, the bf16 top-1 trajectory scan k_traj_mm for bf16 stores, k = 1 and
+    more than 128 queries per launch, and k_traj_scan."""
+    small = s.n < 5000
+    sem = None
+    if s.B_sem:
+        sem = "k_sem_split" if small else ("k_sem_mm" if s.k == 1 else "k_sem_scan")
     traj = None
     if s.B_traj:
-        traj = "k_traj_mm" if (s.map_dtype == "bf16" and s.k == 1 and min(s.B_traj, 1024) > 128) else "k_traj_scan"
+        wide = s.map_dtype == "bf16" and s.k == 1 and min(s.B_traj, 1024) > 128
+        traj = "k_traj_split" if small else ("k_traj_mm" if wide else "k_traj_scan")
     return sem, traj
 
 

@@ -125,7 +125,7 @@ size_t fm_store_bytes(int32_t cap, int32_t L, int32_t E, int32_t d_emb, fm_dtype
  * up to B_max queries keeping up to k_max matches each (device memory,
  * 256-byte aligned, owned by the caller).  It holds the staged queries of one
  * launch (depth-sorted trajectory planes, or tiled semantic embeddings), the
- * query norms and the per-workgroup partial top-k lists.  Every match call
+ * query norms, ranking floors and the per-workgroup partial top-k lists.  Every match call
  * rewrites what it reads, so the contents need no initialisation.  Calls that
  * share a workspace must be ordered (same stream, or synchronised); concurrent
  * calls on one workspace race.  Returns 0 for invalid arguments. */
