@@ -148,7 +148,7 @@ hipError_t launch_match_semantic(const StoreView& s, const void* q, int32_t B, i
 int sem_mm_group(int32_t Bc);
 hipError_t launch_sem_mm(const StoreView& s, int32_t Bc, int32_t b_pad, const Workspace& ws, float* dbg, int32_t* R_out,
                          hipStream_t st, const float* mix = nullptr, double w_self = 1.0, double w_mix = 0.0);
-// Split-k semantic scan (fm_sem_split.hip): whether and how a chunk of Bc
+// Split-k semantic scan (fm_sem_split.hip), top-1 or dense: whether and how a chunk of Bc
 // queries takes it (shape < 0: it takes k_sem_mm), and the scan itself, on
 // queries staged by k_sem_prep in groups of p.group or, with p.raw, on the
 // caller's rows.  Its partial lists (p.R per query) rank by dot / |x|; their
@@ -159,9 +159,9 @@ struct SemSplit {
   int group = 0;      // queries per group
   int R = 0;          // partial lists per query
 };
-SemSplit sem_split_plan(int32_t Bc, int32_t n, int32_t d, int KTOP, bool dense);
+SemSplit sem_split_plan(int32_t Bc, int32_t n, int32_t d, bool dense);
 // (dbg, mix, w_self, w_mix: the dense form, as for launch_sem_mm.)
-hipError_t launch_sem_split(const StoreView& s, const SemSplit& p, const uint16_t* q, int32_t Bc, int KTOP,
+hipError_t launch_sem_split(const StoreView& s, const SemSplit& p, const uint16_t* q, int32_t Bc,
                             const Workspace& ws, hipStream_t st, float* dbg = nullptr, const float* mix = nullptr,
                             double w_self = 1.0, double w_mix = 0.0);
 // Top-1 trajectory scan of bf16 stores (fm_traj_mm.hip): whether a chunk of

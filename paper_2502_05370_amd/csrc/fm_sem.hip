@@ -460,16 +460,17 @@ hipError_t launch_match_semantic(const StoreView& s, const void* q, int32_t B, i
                                  const float* mix, double w_self, double w_mix, const SelectFuse* fuse) {
   const int KTOP = k == 1 ? 1 : (k <= 4 ? 4 : 8);
   const int n_blocks = (s.n + 15) / 16;
-  // The split-k scan where it is the faster one (fm_sem_split.hip); else one
-  // match, and the dense form (no matches returned), on k_sem_mm
-  // (fm_sem_mm.hip) and lists of 4 or 8 here.
+  // One match, and the dense form (no matches returned), on the split-k scan
+  // where it is the faster one (fm_sem_split.hip), else on k_sem_mm
+  // (fm_sem_mm.hip); lists of 4 or 8 here.
   const bool mm = dbg_scores != nullptr || KTOP == 1;
   for (int b0 = 0; b0 < B; b0 += kChunkB) {
     const int Bc = (B - b0) < kChunkB ? (B - b0) : kChunkB;
     int TQ = 1;
     while (16 * TQ < Bc && TQ < kSemTq) TQ *= 2;
     if (mm) TQ = sem_mm_group(Bc) / 16;
-    const SemSplit sp = sem_split_plan(Bc, s.n, s.d_emb, dbg_scores != nullptr ? 1 : KTOP, dbg_scores != nullptr);
+    SemSplit sp;
+    if (mm) sp = sem_split_plan(Bc, s.n, s.d_emb, dbg_scores != nullptr);
     float* dbg_b = dbg_scores != nullptr ? dbg_scores + static_cast<int64_t>(b0) * s.n : nullptr;
     const float* mix_b = mix != nullptr ? mix + static_cast<int64_t>(b0) * s.n : nullptr;
     const int QG = sp.shape >= 0 ? sp.group : 16 * TQ;
@@ -490,7 +491,7 @@ hipError_t launch_match_semantic(const StoreView& s, const void* q, int32_t B, i
       if (err != hipSuccess) return err;
     }
     if (sp.shape >= 0) {
-      err = launch_sem_split(s, sp, pa.q, Bc, KTOP, ws, st, dbg_b, mix_b, w_self, w_mix);
+      err = launch_sem_split(s, sp, pa.q, Bc, ws, st, dbg_b, mix_b, w_self, w_mix);
       if (err != hipSuccess) return err;
       if (dbg_b != nullptr) continue;
       err = fuse != nullptr

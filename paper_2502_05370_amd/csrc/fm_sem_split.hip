@@ -2,8 +2,11 @@
 //
 // The contraction Q X^T of a query batch (B x d) with the stored embeddings
 // (n x d), both bf16 on v_mfma_f32_16x16x32_bf16 as in k_sem_mm
-// (fm_sem_mm.hip), for the searches whose time is not the matrix rate: small
-// stores and small batches, and every search that keeps 2 to 8 matches.
+// (fm_sem_mm.hip), for top-1 searches whose time is not the matrix rate: small
+// stores and small batches.  (Top-2..8 lists stay on k_sem_scan: this scan's
+// sums differ from a sequential one by up to 1e-6 of a cosine, and the last
+// place of a list of 8 is near enough a tie in about one query of a hundred to
+// change hands for it, with that query's blended sets.)
 //
 // A workgroup takes a group of 16 TQ queries and a range of the store's 16-map
 // blocks, NB blocks per step.  Its W wavefronts split the d dimensions: each
@@ -14,7 +17,7 @@
 // k-steps, and a store of only a few blocks still fills a workgroup per
 // block.  At the end of a step the W partial tiles are summed through LDS,
 // each (block, query tile) pair by one wavefront, which scales the sums by
-// 1/|x| and keeps its query tile's best in per-lane top-K lists.
+// 1/|x| and keeps its query tile's best per lane.
 //
 // The dense form writes every cosine, or its weighted sum with a second
 // dense matrix (the deduplicating insert's RDY), instead of keeping lists.
@@ -64,6 +67,8 @@ struct SplitArgs {
   int32_t grid;
 };
 
+constexpr int KTOP = 1;   // matches kept per query
+
 template <int W, int NB, int TQ>
 struct SplitShape {
   static constexpr int TC0 = W * NB * TQ <= 128 ? TQ : 128 / (W * NB);   // query tiles per reduction phase (128 KB of LDS)
@@ -83,7 +88,7 @@ __device__ __forceinline__ uint64_t split_key(float s, int32_t idx) {
 
 }  // namespace
 
-template <int W, int NB, int TQ, int D, int KTOP, bool RAW, bool DENSE>
+template <int W, int NB, int TQ, int D, bool RAW, bool DENSE>
 __global__ void __launch_bounds__(W * 64) __attribute__((amdgpu_waves_per_eu(W / 4, W / 4))) k_sem_split(SplitArgs a) {
   using S = SplitShape<W, NB, TQ>;
   constexpr int TC = S::TC, PAIRS = S::PAIRS, PH = S::PH;
@@ -332,7 +337,7 @@ __global__ void __launch_bounds__(W * 64) __attribute__((amdgpu_waves_per_eu(W /
 
 namespace {
 
-template <int W, int NB, int TQ, int D, int KTOP, bool RAW, bool DENSE = false>
+template <int W, int NB, int TQ, int D, bool RAW, bool DENSE = false>
 hipError_t split_launch(const SplitArgs& a, hipStream_t st) {
   using S = SplitShape<W, NB, TQ>;
   constexpr size_t red = static_cast<size_t>(W) * S::PAIRS * 1024;
@@ -340,7 +345,7 @@ hipError_t split_launch(const SplitArgs& a, hipStream_t st) {
   constexpr size_t lds = red > mrg ? red : mrg;
   static_assert(lds <= 160 * 1024, "LDS");
   static_assert(!(RAW && DENSE), "the dense form reads 1/|q| in the scan");
-  auto kern = k_sem_split<W, NB, TQ, D, KTOP, RAW, DENSE>;
+  auto kern = k_sem_split<W, NB, TQ, D, RAW, DENSE>;
   if (lds > 64 * 1024) {
     const hipError_t err = hipFuncSetAttribute(reinterpret_cast<const void*>(kern),
                                                hipFuncAttributeMaxDynamicSharedMemorySize, static_cast<int>(lds));
@@ -369,16 +374,13 @@ struct ShapeInfo {
 constexpr ShapeInfo kShapes[] = {{1, 1, true, 0.05, 5.0e6},   {4, 1, true, 0.075, 5.7e6}, {4, 2, true, 0.16, 4.6e6},
                                  {4, 4, false, 0.15, 5.0e6},  {4, 8, false, 0.24, 5.0e6}};
 
-template <int KTOP>
 hipError_t split_shape(int shape, const SplitArgs& a, hipStream_t st) {
   switch (shape) {
-    case 0: return split_launch<8, 1, 1, 4, KTOP, true>(a, st);
-    case 1: return split_launch<8, 4, 1, 4, KTOP, true>(a, st);
-    case 2: return split_launch<8, 4, 2, 4, KTOP, true>(a, st);
-    case 3: return split_launch<8, 4, 4, 2, KTOP, false>(a, st);
-    case 4:
-      if constexpr (KTOP < 8) return split_launch<8, 4, 8, 2, KTOP, false>(a, st);
-      return hipErrorInvalidValue;
+    case 0: return split_launch<8, 1, 1, 4, true>(a, st);
+    case 1: return split_launch<8, 4, 1, 4, true>(a, st);
+    case 2: return split_launch<8, 4, 2, 4, true>(a, st);
+    case 3: return split_launch<8, 4, 4, 2, false>(a, st);
+    case 4: return split_launch<8, 4, 8, 2, false>(a, st);
     default: return hipErrorInvalidValue;
   }
 }
@@ -393,7 +395,6 @@ int split_workgroups(int n_qg, int n_blocks, int nb) {
 
 constexpr double kPrepUs = 5.0;       // k_sem_prep
 constexpr double kMmUs = 0.75;        // a k-step of a k_sem_mm slice (its stage)
-constexpr double kScanUs = 0.5;       // a k-step of a k_sem_scan slice
 constexpr double kMmRate = 5.8e6;
 
 }  // namespace
@@ -406,16 +407,16 @@ constexpr double kMmRate = 5.8e6;
 // queries 24.6 against 93; 16,000 of d = 2048, 8 queries 13 against 51, 100
 // queries 25.7 against 51, 1,000 queries 120 against 58.7; 60,000 of d = 2048,
 // 30 queries 50 against 59, 128 queries 82 against 60.
-SemSplit sem_split_plan(int32_t Bc, int32_t n, int32_t d, int KTOP, bool dense) {
+SemSplit sem_split_plan(int32_t Bc, int32_t n, int32_t d, bool dense) {
   const int n_blocks = (n + 15) / 16;
   const int ksteps = d / 32;
   const double bytes = 2.0 * n * d;
-  // the full-width scans: k_sem_mm (one match) or k_sem_scan
-  const int QG = KTOP == 1 ? sem_mm_group(Bc) : 64;
-  const int SB = KTOP == 1 && QG == 128 ? 32 : 16;
+  // the full-width scan, k_sem_mm
+  const int QG = sem_mm_group(Bc);
+  const int SB = QG == 128 ? 32 : 16;
   const int R0 = split_workgroups((Bc + QG - 1) / QG, n_blocks, 1);
   const double slices = ((n_blocks + R0 - 1) / R0 + SB - 1) / SB;
-  double best = slices * ksteps * (KTOP == 1 ? kMmUs : kScanUs);
+  double best = slices * ksteps * kMmUs;
   if (best < bytes / kMmRate) best = bytes / kMmRate;
   best += kPrepUs;
   SemSplit p;
@@ -423,7 +424,6 @@ SemSplit sem_split_plan(int32_t Bc, int32_t n, int32_t d, int KTOP, bool dense) 
     const ShapeInfo& si = kShapes[i];
     const int n_qg = (Bc + 16 * si.tq - 1) / (16 * si.tq);
     if (dense && si.raw) continue;
-    if (si.tq == 8 && KTOP == 8) continue;   // its lists do not fit the registers (19 spilled, 72 -> 95 us)
     const int R = split_workgroups(n_qg, n_blocks, si.nb);
     const double steps = ((n_blocks + R - 1) / R + si.nb - 1) / si.nb;
     double t = steps * ksteps * si.step_us;
@@ -440,7 +440,7 @@ SemSplit sem_split_plan(int32_t Bc, int32_t n, int32_t d, int KTOP, bool dense) 
   return p;
 }
 
-hipError_t launch_sem_split(const StoreView& s, const SemSplit& p, const uint16_t* q, int32_t Bc, int KTOP,
+hipError_t launch_sem_split(const StoreView& s, const SemSplit& p, const uint16_t* q, int32_t Bc,
                             const Workspace& ws, hipStream_t st, float* dbg, const float* mix, double w_self,
                            double w_mix) {
   SplitArgs a;
@@ -463,13 +463,11 @@ hipError_t launch_sem_split(const StoreView& s, const SemSplit& p, const uint16_
   a.n_blocks = (s.n + 15) / 16;
   a.grid = (a.n_qg * a.R + 7) / 8 * 8;
   if (dbg != nullptr) {
-    if (p.shape == 3) return split_launch<8, 4, 4, 2, 1, false, true>(a, st);
-    if (p.shape == 4) return split_launch<8, 4, 8, 2, 1, false, true>(a, st);
+    if (p.shape == 3) return split_launch<8, 4, 4, 2, false, true>(a, st);
+    if (p.shape == 4) return split_launch<8, 4, 8, 2, false, true>(a, st);
     return hipErrorInvalidValue;
   }
-  if (KTOP == 1) return split_shape<1>(p.shape, a, st);
-  if (KTOP == 4) return split_shape<4>(p.shape, a, st);
-  return split_shape<8>(p.shape, a, st);
+  return split_shape(p.shape, a, st);
 }
 
 }  // namespace fm
