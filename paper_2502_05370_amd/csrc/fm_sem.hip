@@ -7,7 +7,7 @@
 // Stored embeddings are kept as 1 KB MFMA operand tiles (emb_offset), so every
 // operand load is one contiguous 1 KB read.  A batch of up to 1024 queries
 // that keeps 2 to 8 matches is served by three launches (one match:
-// fm_sem_mm.hip; small searches: fm_sem_split.hip):
+// fm_sem_mm.hip, and fm_sem_split.hip on small stores):
 //
 //  k_sem_prep   copies the queries into the same tile layout (zero rows pad
 //               the last 16-query tile) and writes 1/|q| (float64 sum).
