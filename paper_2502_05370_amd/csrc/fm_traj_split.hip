@@ -11,9 +11,11 @@
 // partial tiles are summed through LDS, each (block, query tile) pair by one
 // wavefront, which scales the sums by the two prefix inverse norms at the
 // query's depth and keeps its query tile's best in per-lane top-K lists.  A
-// query's staged rows are zero past its depth, so shallower queries of a
-// group add zeros.  Operands, products and their float16 split are those of
-// the general scan.
+// query tile takes part in the layer groups that its deepest query reaches, as
+// in the general scan (so a NaN or infinity stored in a deep layer stays out
+// of shallower tiles); shallower queries of a tile add zeros, as their staged
+// rows are zero past their depth.  Operands, products and their float16 split
+// are those of the general scan.
 //
 // Measured (scan alone): 1,000 float32 maps of 24 x 60, 8 queries 25.5 -> 6.1
 // us; of 32 x 8 9.2 -> 4.5 us; 4,000 bf16 maps of 24 x 60, 100 queries 30.3 ->
@@ -173,6 +175,32 @@ __global__ void __launch_bounds__(kSW * 64) __attribute__((amdgpu_waves_per_eu(2
   const float rq = a.rq[g0 + 16 * tt + c];
   const float* rrow = a.rnorm + static_cast<int64_t>(p > 0 ? p - 1 : 0) * a.rn_stride + 4 * g;
 
+  // depth of each tile's deepest query, its first position
+  int tmd[TQ];
+#pragma unroll
+  for (int t = 0; t < TQ; ++t) tmd[t] = __builtin_amdgcn_readfirstlane(a.sdep[g0 + 16 * t]);
+
+  // products of the k-step in registers s for the first NT query tiles
+  auto products = [&](auto nt_const, int s, const u16x8 (&ap)[NP][NB]) __attribute__((always_inline)) {
+    constexpr int NT = decltype(nt_const)::value;
+    if constexpr (BF) {
+#pragma unroll
+      for (int t = 0; t < NT; ++t)
+#pragma unroll
+        for (int i = 0; i < NB; ++i) acc[i][t] = mfma_bf16(ap[0][i], fq[s][0][t], acc[i][t]);
+    } else {
+      // hi x lo, hi x hi, lo x hi
+      constexpr int TA[3] = {0, 0, 1};
+      constexpr int TB[3] = {1, 0, 0};
+#pragma unroll
+      for (int term = 0; term < 3; ++term)
+#pragma unroll
+        for (int t = 0; t < NT; ++t)
+#pragma unroll
+          for (int i = 0; i < NB; ++i) acc[i][t] = mfma_f16(ap[TA[term]][i], fq[s][TB[term]][t], acc[i][t]);
+    }
+  };
+
   for (int step = 0; step < n_steps; ++step) {
     for (int ki = 0; ki < kp; ki += D) {
 #pragma unroll
@@ -183,23 +211,16 @@ __global__ void __launch_bounds__(kSW * 64) __attribute__((amdgpu_waves_per_eu(2
           if constexpr (BF) ap[0][i] = fm[s][i];
           else split2(fm[s][i], ap[0][i], ap[NP - 1][i]);
         }
-        if constexpr (BF) {
+        // the tiles whose deepest query reaches this layer group (positions
+        // are sorted by depth, so they come first; tile 0 always does)
+        const int l_first = (u0 + ki + s) / KSG * a.geo.lpg;
+        int na = 1;
 #pragma unroll
-          for (int t = 0; t < TQ; ++t)
-#pragma unroll
-            for (int i = 0; i < NB; ++i) acc[i][t] = mfma_bf16(ap[0][i], fq[s][0][t], acc[i][t]);
-        } else {
-          // hi x lo, hi x hi, lo x hi
-          constexpr int TA[3] = {0, 0, 1};
-          constexpr int TB[3] = {1, 0, 0};
-#pragma unroll
-          for (int term = 0; term < 3; ++term)
-#pragma unroll
-            for (int t = 0; t < TQ; ++t)
-#pragma unroll
-              for (int i = 0; i < NB; ++i)
-                acc[i][t] = mfma_f16(ap[TA[term]][i], fq[s][TB[term]][t], acc[i][t]);
-        }
+        for (int t = 1; t < TQ; ++t) na += tmd[t] > l_first ? 1 : 0;
+        if (TQ == 1 || na == 1) products(std::integral_constant<int, 1>{}, s, ap);
+        else if (TQ == 2 || na == 2) products(std::integral_constant<int, TQ < 2 ? TQ : 2>{}, s, ap);
+        else if (na == 3) products(std::integral_constant<int, TQ < 3 ? TQ : 3>{}, s, ap);
+        else products(std::integral_constant<int, TQ>{}, s, ap);
         load(s);
         __builtin_amdgcn_sched_barrier(0);
       }
