@@ -17,6 +17,8 @@
 //      [k_min, k_max]; the mask is the ballot of lanes with rank < k.  Past
 //      k_max entries the sum cannot change the clamped size, so it stops
 //      there.
+#include <cstddef>
+
 #include "fm_device.h"
 #include "fm_guide.h"
 #include "fm_internal.h"
@@ -116,11 +118,13 @@ __device__ __forceinline__ int rank_row(const uint64_t* row, uint64_t mine, int 
 }
 
 // LDS of one wavefront's rows: the keys (64-bit for blended rows, 32-bit
-// otherwise) and the probabilities in rank order.
+// otherwise; rank_row reads them 16 bytes at a time) and the probabilities in
+// rank order.
 struct SelLds {
-  uint64_t keys[kMaxE];
+  __align__(16) uint64_t keys[kMaxE];
   double sorted[kMaxE];
 };
+static_assert(alignof(SelLds) == 16 && offsetof(SelLds, keys) % 16 == 0, "16-byte reads of the keys");
 
 // The selection of row (b, l) of the batch by the SW lanes that hold it
 // (`in`: whether they hold one), from the query's matches idx_b / score_b (k
@@ -218,8 +222,9 @@ __device__ __forceinline__ void select_row(const SelArgs& a, bool in, int b, int
   }
 }
 
-// Rows per wavefront for E experts: lanes per row.
 constexpr int kMergeGroups = 1536;   // workgroups of a merge-and-select launch beyond which positions stop splitting
+
+// Lanes per row for E experts.
 inline int select_width(int E) { return E <= 8 ? 8 : (E <= 16 ? 16 : (E <= 32 ? 32 : 64)); }
 
 template <int SW>
