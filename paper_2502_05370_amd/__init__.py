@@ -72,13 +72,19 @@ def _dev(store: "Store") -> torch.device:
     return store.device
 
 
+# The current stream's handle as an integer.  Not public in torch, so it may be
+# missing; building a torch.cuda.Stream instead costs 2.8 us per call, as much
+# as a kernel launch.
+_raw_stream = getattr(torch._C, "_cuda_getCurrentRawStream", None)
+
+
 def _stream(stream) -> int:
-    """The hipStream_t of ``stream``, or of the current stream (read as an
-    integer: building a torch.cuda.Stream for it costs 2.8 us per call, as
-    much as a kernel launch)."""
-    if stream is None:
-        return torch._C._cuda_getCurrentRawStream(torch.cuda.current_device())
-    return stream.cuda_stream
+    """The hipStream_t of ``stream``, or of the current stream."""
+    if stream is not None:
+        return stream.cuda_stream
+    if _raw_stream is None:
+        return torch.cuda.current_stream().cuda_stream
+    return _raw_stream(torch.cuda.current_device())
 
 
 def _aligned_bytes(nbytes: int, device) -> torch.Tensor:

@@ -75,3 +75,14 @@ def test_checks_in_order(monkeypatch):
         fm.match_trajectory(s, q, None)
     with pytest.raises(TypeError):
         fm.match_trajectory(s, q, [1, 2, 3])
+
+
+def test_current_stream_without_the_raw_handle(monkeypatch):
+    """A torch without the private raw-stream call: the public one serves."""
+    monkeypatch.setattr(torch.cuda, "current_device", lambda: 0)
+    monkeypatch.setattr(torch.cuda, "current_stream", lambda: types.SimpleNamespace(cuda_stream=0x7000))
+    monkeypatch.setattr(fm, "_raw_stream", None)
+    assert fm._stream(None) == 0x7000
+    monkeypatch.setattr(fm, "_raw_stream", lambda device: 0x9000 + device)
+    assert fm._stream(None) == 0x9000
+    assert fm._stream(types.SimpleNamespace(cuda_stream=0x5000)) == 0x5000
