@@ -353,6 +353,18 @@ fm_status fm_debug_scores(const fm_store* store, const void* q, const int32_t* d
                           int32_t max_depth, const void* q_sem, int32_t B, float* scores_out,
                           void* workspace, size_t workspace_bytes, void* stream);
 
+/* Test support: the scan kernel that a match call launches for a batch of B
+ * queries keeping k matches (its first 1,024 queries, if there are more) on a
+ * store of n iterations of L x E maps and d_emb-wide embeddings: a trajectory
+ * search to max_depth >= 1, or a semantic search with max_depth = 0.  k = 0
+ * names the dense form (fm_debug_scores).  A name, then for a kernel of several
+ * shapes a space and the shape: "k_traj_scan", "k_traj_mm", "k_traj_split RxC"
+ * (blocks of 16 maps by tiles of 16 queries), "k_sem_scan", "k_sem_mm Q"
+ * (queries per group), "k_sem_split RxC".  A constant string; NULL for sizes
+ * that the match calls refuse.  Runs on the host, without a GPU. */
+const char* fm_debug_scan_name(int32_t L, int32_t E, int32_t d_emb, fm_dtype map_dtype, int32_t n,
+                               int32_t max_depth, int32_t B, int32_t k);
+
 /* Measurement support: start and stop are hipEvent_t handles (passed as
  * void*) created by the caller, or both NULL to switch this off.  While set,
  * every match call made on this thread records start on its stream right

@@ -33,7 +33,7 @@ _lib.load()
 
 __all__ = ["Store", "Workspace", "match_semantic", "match_trajectory", "match_trajectory_noalloc", "select_prefetch", "priority_order",
            "miss_count",
-           "debug_scores",
+           "debug_scores", "debug_scan_name",
            "map_bytes", "store_bytes", "workspace_bytes", "dedup_scratch_bytes", "traj_state_bytes", "TrajPass",
            "FmError"]
 
@@ -478,3 +478,15 @@ def debug_scores(store: Store, q: Optional[torch.Tensor] = None, depth: Optional
                                            max_depth if max_depth is not None else store.L, _ptr(q_sem), B,
                                            _ptr(out), ws.buf.data_ptr(), ws.nbytes, _stream(stream)), "fm_debug_scores")
     return out[:, :n]
+
+
+def debug_scan_name(L: int, E: int, n: int, B: int, k: int = 1, map_dtype: str = "f32", d_emb: int = 0,
+                    max_depth: Optional[int] = None) -> str:
+    """The scan kernel of a match call with these sizes (fm_debug_scan_name): a
+    trajectory search to ``max_depth`` (default L), or with ``d_emb`` set and no
+    ``max_depth`` a semantic one.  k = 0: the dense form."""
+    depth = max_depth if max_depth is not None else (0 if d_emb else L)
+    name = _lib.load().fm_debug_scan_name(L, E, d_emb, _DTYPES[map_dtype], n, depth, B, k)
+    if name is None:
+        raise ValueError(f"no match call takes L={L} E={E} n={n} B={B} k={k} d_emb={d_emb} max_depth={depth}")
+    return name.decode()

@@ -67,6 +67,7 @@ SIGNATURES = {
     "fm_traj_state_bytes": (_sz, [_i32, _i32]),
     "fm_traj_step": (C.c_int, [_vp, _vp, _sz, _vp, _i32, _i32, _i32, _vp, _vp, _vp, _sz, _vp]),
     "fm_debug_scores": (C.c_int, [_vp, _vp, _vp, _i32, _vp, _i32, _vp, _vp, _sz, _vp]),
+    "fm_debug_scan_name": (C.c_char_p, [_i32, _i32, _i32, C.c_int, _i32, _i32, _i32, _i32]),
     "fm_debug_scan_events": (C.c_int, [_vp, _vp]),
     "fm_last_error": (C.c_char_p, []),
     "fm_version": (C.c_int32, []),

@@ -535,6 +535,16 @@ fm_status fm_debug_scores(const fm_store* s, const void* q, const int32_t* depth
   return ok();
 }
 
+const char* fm_debug_scan_name(int32_t L, int32_t E, int32_t d_emb, fm_dtype map_dtype, int32_t n, int32_t max_depth,
+                               int32_t B, int32_t k) {
+  if (L < 1 || L > fm::kMaxL || E < 1 || E > fm::kMaxE || !valid_dtype(map_dtype)) return nullptr;
+  if (d_emb < 0 || d_emb % 128 != 0 || max_depth < 0 || max_depth > L || (max_depth == 0 && d_emb == 0)) return nullptr;
+  if (n < 0 || B < 1 || B > 65536 || k < 0 || k > fm::kMaxK) return nullptr;
+  const int32_t Bc = B < fm::kChunkB ? B : fm::kChunkB;
+  return max_depth > 0 ? fm::traj_scan_name(map_dtype == FM_BF16, E, n, Bc, k, max_depth)
+                       : fm::sem_scan_name(n, d_emb, Bc, k);
+}
+
 // ---------------------------------------------------------------- allocation-free trajectory search
 
 }  // extern "C"

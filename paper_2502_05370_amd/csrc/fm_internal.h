@@ -160,6 +160,7 @@ struct SemSplit {
   int R = 0;          // partial lists per query
 };
 SemSplit sem_split_plan(int32_t Bc, int32_t n, int32_t d, bool dense);
+const char* sem_split_name(const SemSplit& p);
 // (dbg, mix, w_self, w_mix: the dense form, as for launch_sem_mm.)
 hipError_t launch_sem_split(const StoreView& s, const SemSplit& p, const uint16_t* q, int32_t Bc,
                             const Workspace& ws, hipStream_t st, float* dbg = nullptr, const float* mix = nullptr,
@@ -173,6 +174,10 @@ int traj_mm_group();
 int traj_mm_workgroups();
 hipError_t launch_traj_mm(const StoreView& s, int spl, int lpg, int ksg, int nlg, int32_t max_depth, int32_t b_pad,
                           const Workspace& ws, float* dbg, int32_t* R_out, hipStream_t st);
+// The scan that the match launchers take for a launch of Bc queries (k = 0: the
+// dense form), by the name that fm_debug_scan_name documents.
+const char* traj_scan_name(bool bf, int32_t E, int32_t n, int32_t Bc, int32_t k, int32_t max_depth);
+const char* sem_scan_name(int32_t n, int32_t d, int32_t Bc, int32_t k);
 hipError_t launch_miss(const StoreView& s, const void* q, int32_t B, int32_t K, const uint64_t* masks,
                        const int32_t* lb, const int32_t* le, uint8_t* miss_out, hipStream_t st);
 hipError_t launch_priority(const StoreView& s, const int32_t* idx, const float* score, int32_t B, int32_t k,

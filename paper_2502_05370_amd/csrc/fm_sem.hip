@@ -455,6 +455,12 @@ hipError_t sem_tq(int TQ, const SemArgs& a, hipStream_t st) {
 
 }  // namespace
 
+const char* sem_scan_name(int32_t n, int32_t d, int32_t Bc, int32_t k) {
+  if (k > 1) return "k_sem_scan";
+  const SemSplit p = sem_split_plan(Bc, n, d, k == 0);
+  return p.shape >= 0 ? sem_split_name(p) : (sem_mm_group(Bc) == 256 ? "k_sem_mm 256" : "k_sem_mm 128");
+}
+
 hipError_t launch_match_semantic(const StoreView& s, const void* q, int32_t B, int32_t k, int32_t* idx_out,
                                  float* score_out, float* dbg_scores, const Workspace& ws, hipStream_t st,
                                  const float* mix, double w_self, double w_mix, const SelectFuse* fuse) {

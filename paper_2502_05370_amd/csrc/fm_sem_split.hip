@@ -440,6 +440,12 @@ SemSplit sem_split_plan(int32_t Bc, int32_t n, int32_t d, bool dense) {
   return p;
 }
 
+const char* sem_split_name(const SemSplit& p) {
+  constexpr const char* kNames[] = {"k_sem_split 1x1", "k_sem_split 4x1", "k_sem_split 4x2", "k_sem_split 4x4",
+                                    "k_sem_split 4x8"};
+  return kNames[p.shape];
+}
+
 hipError_t launch_sem_split(const StoreView& s, const SemSplit& p, const uint16_t* q, int32_t Bc,
                             const Workspace& ws, hipStream_t st, float* dbg, const float* mix, double w_self,
                            double w_mix) {

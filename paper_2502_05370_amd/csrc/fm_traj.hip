@@ -1031,6 +1031,8 @@ int scan_rt_bytes(int TQ, int KSG, int dmax, bool bf) {
   return (rows * 8 * nba * 16 * 4 + 8 * 1024 - 1) / (8 * 1024) * (8 * 1024);
 }
 
+constexpr size_t kScanLds = 160 * 1024;   // a workgroup's LDS
+
 // LDS of the scan: 3 ring slots of query planes (8 waves x NI_Q x 1 KB each),
 // two inverse-norm tables, and the group's sorted query info (permutation,
 // depth, 1/|q|, distinct-depth index and values, distinct-depth masks) and
@@ -1113,6 +1115,39 @@ size_t traj_qrows_bytes(int L, int E, fm_dtype dt, int b_pad) {
   return static_cast<size_t>(nlg) * b_pad * np * qrow_bytes(g.ksg) + 16384;
 }
 
+namespace {
+
+// The scan that a launch of Bc queries takes.
+struct TrajPlan {
+  int TQ = 1;         // query tiles per group of k_traj_scan
+  bool mm = false;    // k_traj_mm, unless the split-depth scan is taken
+  TrajSplit split;
+  bool split_taken() const { return split.shape >= 0; }
+};
+
+TrajPlan traj_plan(bool bf, int32_t n, int32_t row, const Geo& geo, int32_t Bc, int KTOP, int32_t max_depth,
+                   bool dense) {
+  const int nlg = (max_depth + geo.lpg - 1) / geo.lpg;
+  TrajPlan p;
+  while (16 * p.TQ < Bc && p.TQ < tq_limit(bf, geo.ksg, KTOP)) p.TQ *= 2;
+  // smaller query groups when the staged planes of one would not fit the ring
+  while (p.TQ > 1 && scan_lds(bf, p.TQ, geo.ksg, KTOP, max_depth) > kScanLds) p.TQ /= 2;
+  p.mm = traj_mm_fits(bf, KTOP, n, Bc, max_depth, nlg, geo.ksg);
+  // the split-depth scan where it is the faster one (fm_traj_split.hip; it
+  // has no dense form)
+  if (!dense) p.split = traj_split_plan(bf, n, row, geo, Bc, nlg, p.TQ, scan_nba(p.TQ, geo.ksg, bf), p.mm);
+  return p;
+}
+
+}  // namespace
+
+const char* traj_scan_name(bool bf, int32_t E, int32_t n, int32_t Bc, int32_t k, int32_t max_depth) {
+  const int KTOP = k <= 1 ? 1 : (k <= 4 ? 4 : 8);
+  const TrajPlan p = traj_plan(bf, n, row_elems(E), geometry(E), Bc, KTOP, max_depth, k == 0);
+  if (p.split_taken()) return traj_split_name(p.split);
+  return p.mm ? "k_traj_mm" : "k_traj_scan";
+}
+
 hipError_t launch_match_trajectory(const StoreView& s, const void* q, const int32_t* depth, int32_t max_depth,
                                    int32_t B, int32_t k, int32_t* idx_out, float* score_out, float* dbg_scores,
                                    const Workspace& ws, hipStream_t st, const SelectFuse* fuse) {
@@ -1121,22 +1156,13 @@ hipError_t launch_match_trajectory(const StoreView& s, const void* q, const int3
   const Geo geo = geometry(s.E);
   // the dense-output form keeps top-1 lists (k = 1)
   const int KTOP = (k == 1 || dbg_scores != nullptr) ? 1 : (k <= 4 ? 4 : 8);
-  const int tq_max = tq_limit(bf, geo.ksg, KTOP);
-  constexpr size_t kLds = 160 * 1024;
-
   const int nlg = (max_depth + geo.lpg - 1) / geo.lpg;
   for (int b0 = 0; b0 < B; b0 += kChunkB) {
     const int Bc = (B - b0) < kChunkB ? (B - b0) : kChunkB;
-    int TQ = 1;
-    while (16 * TQ < Bc && TQ < tq_max) TQ *= 2;
-    // smaller query groups when the staged planes of one would not fit the ring
-    while (TQ > 1 && scan_lds(bf, TQ, geo.ksg, KTOP, max_depth) > kLds) TQ /= 2;
-    // the split-depth scan where it is the faster one (fm_traj_split.hip; it
-    // has no dense form)
-    const bool mm = traj_mm_fits(bf, KTOP, s.n, Bc, max_depth, nlg, geo.ksg);
-    TrajSplit sp;
-    if (dbg_scores == nullptr) sp = traj_split_plan(s, geo, Bc, nlg, TQ, scan_nba(TQ, geo.ksg, bf), mm);
-    if (mm && sp.shape < 0) {
+    const TrajPlan pl = traj_plan(bf, s.n, s.row, geo, Bc, KTOP, max_depth, dbg_scores != nullptr);
+    const int TQ = pl.TQ;
+    const TrajSplit& sp = pl.split;
+    if (pl.mm && !pl.split_taken()) {
       // bf16 top-1 (or dense) batches of more than half a band: k_traj_mm
       const int QG = traj_mm_group();
       const int n_qg = (Bc + QG - 1) / QG;
@@ -1178,7 +1204,7 @@ hipError_t launch_match_trajectory(const StoreView& s, const void* q, const int3
       }
       continue;
     }
-    const int QG = sp.shape >= 0 ? sp.group : 16 * TQ;
+    const int QG = pl.split_taken() ? sp.group : 16 * TQ;
     const int n_qg = (Bc + QG - 1) / QG;
     const int b_pad = n_qg * QG;
 
@@ -1214,7 +1240,7 @@ hipError_t launch_match_trajectory(const StoreView& s, const void* q, const int3
     hipError_t err = hipGetLastError();
     if (err != hipSuccess) return err;
 
-    if (sp.shape >= 0) {
+    if (pl.split_taken()) {
       err = launch_traj_split(s, sp, geo, Bc, b_pad, KTOP, ws, st);
       if (err != hipSuccess) return err;
       err = fuse != nullptr
@@ -1228,7 +1254,7 @@ hipError_t launch_match_trajectory(const StoreView& s, const void* q, const int3
     }
 
     const size_t lds = scan_lds(bf, TQ, geo.ksg, KTOP, max_depth);
-    if (lds > kLds) return hipErrorInvalidConfiguration;
+    if (lds > kScanLds) return hipErrorInvalidConfiguration;
 
     const int R = G;   // partial lists per position (a group's share is at most G)
 

@@ -344,10 +344,10 @@ double scan_stage_us(bool bf, int TQ) {
 // queries 16,000 maps 38.9 / 25.0, 50,000 52.4 / 101; 32 x 8, 8 queries 1,000
 // maps 9.2 / 4.5; bf16 24 x 60, 100 queries 4,000 maps 30.3 / 9.5, 16 queries
 // 200,003 maps 110 / 150; 32 x 16 float32, 1,000 queries 4,000 maps 31.5 / 29.5.
-TrajSplit traj_split_plan(const StoreView& s, const Geo& geo, int32_t Bc, int nlg, int TQ, int nba, bool mm) {
-  const bool bf = s.map_dtype == FM_BF16;
-  const int n_blocks = (s.n + 15) / 16;
-  const double bytes = static_cast<double>(s.n) * nlg * geo.lpg * s.row * (bf ? 2 : 4);
+TrajSplit traj_split_plan(bool bf, int32_t n, int32_t row, const Geo& geo, int32_t Bc, int nlg, int TQ, int nba,
+                          bool mm) {
+  const int n_blocks = (n + 15) / 16;
+  const double bytes = static_cast<double>(n) * nlg * geo.lpg * row * (bf ? 2 : 4);
   double best;
   if (mm) {
     const int slices = (n_blocks + 15) / 16 * ((Bc + traj_mm_group() - 1) / traj_mm_group());
@@ -357,7 +357,7 @@ TrajSplit traj_split_plan(const StoreView& s, const Geo& geo, int32_t Bc, int nl
     int R = 256 / n_qg;
     if (R > n_blocks) R = n_blocks;
     if (R < 1) R = 1;
-    const int maps = (s.n + R - 1) / R;
+    const int maps = (n + R - 1) / R;
     best = static_cast<double>((maps + 128 * nba - 1) / (128 * nba)) * nlg * scan_stage_us(bf, TQ);
   }
   if (best < bytes / kScanRate) best = bytes / kScanRate;
@@ -381,6 +381,10 @@ TrajSplit traj_split_plan(const StoreView& s, const Geo& geo, int32_t Bc, int nl
     }
   }
   return p;
+}
+
+const char* traj_split_name(const TrajSplit& p) {
+  return p.shape == 0 ? "k_traj_split 1x1" : p.shape == 1 ? "k_traj_split 2x2" : "k_traj_split 2x4";
 }
 
 hipError_t launch_traj_split(const StoreView& s, const TrajSplit& p, const Geo& geo, int32_t Bc, int32_t b_pad,

@@ -1,0 +1,33 @@
+"""Which scan kernel serves a match call (fm_debug_scan_name), on the CPU: the
+choice is made on the host from the sizes alone."""
+import pytest
+
+import paper_2502_05370_amd as fm
+
+
+def test_names_follow_the_sizes():
+    name = fm.debug_scan_name
+    assert name(32, 8, 1000, 8) == "k_traj_split 1x1"
+    assert name(24, 60, 1000000, 512, 1, "bf16") == "k_traj_mm"
+    assert name(24, 60, 50000, 64) == "k_traj_scan"
+    assert name(32, 16, 200000, 512, 4) == "k_traj_scan"
+    assert name(32, 8, 1000, 8, d_emb=4096) == "k_sem_split 1x1"
+    assert name(24, 60, 1000000, 512, d_emb=2048) == "k_sem_mm 256"
+    assert name(32, 8, 100000, 100, d_emb=4096) == "k_sem_mm 128"
+    for k in (2, 8):
+        assert name(32, 8, 1000, 8, k, d_emb=4096) == "k_sem_scan"
+    # both kinds on one store: max_depth says which
+    assert name(32, 8, 1000, 8, d_emb=4096, max_depth=5).startswith("k_traj_")
+    # the dense form has no split-depth scan
+    assert name(32, 8, 1000, 8, 0) == "k_traj_scan"
+    # a batch of several launches: its first one
+    assert name(24, 60, 200000, 5000, 1, "bf16") == name(24, 60, 200000, 1024, 1, "bf16")
+
+
+@pytest.mark.parametrize("kw", [dict(L=0), dict(L=65), dict(E=0), dict(E=65), dict(n=-1), dict(B=0), dict(B=65537), dict(k=9),
+                                dict(k=-1), dict(d_emb=100), dict(max_depth=33), dict(max_depth=0)])
+def test_sizes_that_no_call_takes(kw):
+    a = dict(L=32, E=8, n=1000, B=8, k=1, d_emb=0)
+    a.update(kw)
+    with pytest.raises(ValueError, match="no match call"):
+        fm.debug_scan_name(**a)
