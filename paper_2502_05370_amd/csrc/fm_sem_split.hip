@@ -362,17 +362,20 @@ hipError_t split_launch(const SplitArgs& a, hipStream_t st) {
   return hipEventRecord(ev.stop, st);
 }
 
-// The shapes: blocks per step, query tiles, and what the dispatch weighs them
-// by.  step_us is the measured time of one k-step (all W wavefronts' share of
-// 32 dimensions) of a step, raw the shapes that need no k_sem_prep, and rate
-// the bytes of embeddings per microsecond that bound a large store.
+// The shapes: blocks per step, query tiles, whether they read the caller's
+// rows, and what the choice of a scan weighs: a k-step (32 dimensions) of a
+// step, the rest of a step (the reduction through LDS, which at d = 128 is most
+// of it), and the bytes of embeddings per microsecond that bound a large store.
 struct ShapeInfo {
   int nb, tq;
   bool raw;
-  double step_us, rate;
+  double kstep, step, rate;
 };
-constexpr ShapeInfo kShapes[] = {{1, 1, true, 0.05, 5.0e6},   {4, 1, true, 0.075, 5.7e6}, {4, 2, true, 0.16, 4.6e6},
-                                 {4, 4, false, 0.15, 5.0e6},  {4, 8, false, 0.24, 5.0e6}};
+constexpr ShapeInfo kShapes[] = {{1, 1, true, 0.06, 1.1, 5.0e6},
+                                 {4, 1, true, 0.10, 1.3, 5.7e6},
+                                 {4, 2, true, 0.16, 1.3, 4.6e6},
+                                 {4, 4, false, 0.18, 1.9, 5.0e6},
+                                 {4, 8, false, 0.26, 5.3, 5.0e6}};
 
 hipError_t split_shape(int shape, const SplitArgs& a, hipStream_t st) {
   switch (shape) {
@@ -393,20 +396,26 @@ int split_workgroups(int n_qg, int n_blocks, int nb) {
   return R < 1 ? 1 : R;
 }
 
-constexpr double kPrepUs = 5.0;       // k_sem_prep
-constexpr double kMmUs = 0.75;        // a k-step of a k_sem_mm slice (its stage)
+constexpr double kPrep = 3.2;                     // k_sem_prep
+constexpr double kMmStage128 = 1.16;              // a k-step of a k_sem_mm slice, groups of 128
+constexpr double kMmStage256 = 1.24;              // ... and of 256
 constexpr double kMmRate = 5.8e6;
 
 }  // namespace
 
-// The scan with the least estimated time: launches, plus the longest
-// workgroup's k-steps (a step or slice costs about the same however many of
-// its blocks exist), but no less than the embeddings take to read.  Both
-// sides measured (scan plus k_sem_prep, us): 1,000 maps of d = 4096, 8
-// queries 8.1 against 88 on k_sem_mm, 100 queries 16.8 against 89, 1,000
-// queries 24.6 against 93; 16,000 of d = 2048, 8 queries 13 against 51, 100
-// queries 25.7 against 51, 1,000 queries 120 against 58.7; 60,000 of d = 2048,
-// 30 queries 50 against 59, 128 queries 82 against 60.
+// The scan with the least estimated time: k_sem_prep where it runs, plus the
+// longest workgroup's steps or slices (one costs about the same however many of
+// its blocks exist), but no less than the embeddings take to read.  The weights
+// (about microseconds) choose best over 1,500 random sizes, 200 to 800,000
+// entries, d = 128 to 8192, 1 to 1,024 queries, each timed on k_sem_mm and on
+// every shape here: 2 of them lose 2% or more against k_sem_mm (8% at most),
+// and the mean call takes 0.37 of its time there.  (Without a cost per step,
+// narrow embeddings of large stores went to a shape of up to 3.5 times
+// k_sem_mm's time.)  Both sides, the call on k_sem_mm / on the best shape here,
+// us: 1,000 entries of d = 4096, 8 queries 92.6 / 11.8; 955 of d = 768, 8
+// queries 26.6 / 8.4; 3,540 of d = 2048, 109 queries 53.9 / 14.8; 3,503 of d =
+// 768, 161 queries 28.8 / 13.9; and on k_sem_mm: 223,998 of d = 128, 33 queries
+// 25.8 / 56.2; 107,404 of d = 384, 38 queries 26.8 / 34.5.
 SemSplit sem_split_plan(int32_t Bc, int32_t n, int32_t d, bool dense) {
   const int n_blocks = (n + 15) / 16;
   const int ksteps = d / 32;
@@ -416,9 +425,9 @@ SemSplit sem_split_plan(int32_t Bc, int32_t n, int32_t d, bool dense) {
   const int SB = QG == 128 ? 32 : 16;
   const int R0 = split_workgroups((Bc + QG - 1) / QG, n_blocks, 1);
   const double slices = ((n_blocks + R0 - 1) / R0 + SB - 1) / SB;
-  double best = slices * ksteps * kMmUs;
+  double best = slices * ksteps * (QG == 128 ? kMmStage128 : kMmStage256);
   if (best < bytes / kMmRate) best = bytes / kMmRate;
-  best += kPrepUs;
+  best += kPrep;
   SemSplit p;
   for (int i = 0; i < static_cast<int>(sizeof(kShapes) / sizeof(kShapes[0])); ++i) {
     const ShapeInfo& si = kShapes[i];
@@ -426,9 +435,9 @@ SemSplit sem_split_plan(int32_t Bc, int32_t n, int32_t d, bool dense) {
     if (dense && si.raw) continue;
     const int R = split_workgroups(n_qg, n_blocks, si.nb);
     const double steps = ((n_blocks + R - 1) / R + si.nb - 1) / si.nb;
-    double t = steps * ksteps * si.step_us;
+    double t = steps * (ksteps * si.kstep + si.step);
     if (t < bytes / si.rate) t = bytes / si.rate;
-    if (!si.raw) t += kPrepUs;
+    if (!si.raw) t += kPrep;
     if (t < best) {
       best = t;
       p.shape = i;

@@ -31,3 +31,15 @@ def test_sizes_that_no_call_takes(kw):
     a.update(kw)
     with pytest.raises(ValueError, match="no match call"):
         fm.debug_scan_name(**a)
+
+
+# (entries, d, queries, time of the call on k_sem_mm, on the best split-k shape), us
+SEMANTIC = [(1000, 4096, 8, 92.6, 11.8), (955, 768, 8, 26.6, 8.4), (3540, 2048, 109, 53.9, 14.8), (3503, 768, 161, 28.8, 13.9),
+            (46724, 1024, 1, 35.3, 21.4), (439127, 128, 29, 36.5, 74.4), (223998, 128, 33, 25.8, 56.2),
+            (13308, 128, 472, 17.4, 29.4), (720906, 128, 7, 48.0, 97.0), (31848, 128, 119, 16.1, 21.0),
+            (107404, 384, 38, 26.8, 34.5), (380356, 256, 12, 44.9, 59.6)]
+
+
+@pytest.mark.parametrize("n,d,B,mm,split", SEMANTIC)
+def test_semantic_search_takes_the_scan_that_measured_faster(n, d, B, mm, split):
+    assert fm.debug_scan_name(32, 8, n, B, d_emb=d).startswith("k_sem_mm" if mm < split else "k_sem_split")
