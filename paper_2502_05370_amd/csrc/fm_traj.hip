@@ -1135,7 +1135,7 @@ TrajPlan traj_plan(bool bf, int32_t n, int32_t row, const Geo& geo, int32_t Bc, 
   p.mm = traj_mm_fits(bf, KTOP, n, Bc, max_depth, nlg, geo.ksg);
   // the split-depth scan where it is the faster one (fm_traj_split.hip; it
   // has no dense form)
-  if (!dense) p.split = traj_split_plan(bf, n, row, geo, Bc, nlg, p.TQ, scan_nba(p.TQ, geo.ksg, bf), p.mm);
+  if (!dense) p.split = traj_split_plan(bf, n, row, geo, Bc, KTOP, nlg, p.TQ, scan_nba(p.TQ, geo.ksg, bf), p.mm);
   return p;
 }
 

@@ -77,8 +77,8 @@ struct TrajSplit {
 };
 // (nlg: the layer groups that max_depth reaches; mm, or TQ and nba: the scan
 // that would run otherwise.)
-TrajSplit traj_split_plan(bool bf, int32_t n, int32_t row, const Geo& geo, int32_t Bc, int nlg, int TQ, int nba,
-                          bool mm);
+TrajSplit traj_split_plan(bool bf, int32_t n, int32_t row, const Geo& geo, int32_t Bc, int KTOP, int nlg, int TQ,
+                          int nba, bool mm);
 const char* traj_split_name(const TrajSplit& p);
 hipError_t launch_traj_split(const StoreView& s, const TrajSplit& p, const Geo& geo, int32_t Bc, int32_t b_pad,
                              int KTOP, const Workspace& ws, hipStream_t st);

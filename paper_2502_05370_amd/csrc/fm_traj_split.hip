@@ -318,47 +318,74 @@ hipError_t split_k(int KTOP, int shape, const SplitTrajArgs& a, hipStream_t st) 
   return split_shape<BF, KSG, 8>(shape, a, st);
 }
 
-// The shapes: blocks per step, query tiles, and the measured microseconds of
-// one of a wavefront's k-steps (float32, bf16).
+// The shapes: blocks per step and query tiles.
 struct ShapeInfo {
   int nb, tq;
-  double f32_us, bf16_us;
 };
-constexpr ShapeInfo kShapes[] = {{1, 1, 0.62, 0.5}, {2, 2, 1.1, 0.75}, {2, 4, 1.85, 1.1}};
+constexpr ShapeInfo kShapes[] = {{1, 1}, {2, 2}, {2, 4}};
+
+// What the choice of a scan weighs (about microseconds).
+struct Weights {
+  double stage[4];    // a stage (layer group of a slice) of k_traj_scan with 1, 2, 4 and 8 query tiles
+  double two_ksteps;  // ... times this where a layer group is two k-steps
+  double slice;       // a slice of k_traj_scan
+  double score[3];    // ... and the ranking of 8 (map block, query tile) pairs of it in lists of 1, 4 and 8
+  double mm_stage;    // a k-step of a k_traj_mm slice
+  double mm_slice;    // a slice of it
+  double kstep[3];    // a k-step of a wavefront of k_traj_split, by shape
+  double step[3];     // the rest of a step of it
+  double lists[3];    // ... times this for lists of 1, 4 and 8
+};
+constexpr Weights kF32 = {{0.8, 1.05, 1.2, 1.4}, 1.5, 2.4, {3.0, 9.6, 10.2}, 0.0, 0.0,
+                          {0.75, 1.35, 2.2}, {0.8, 1.3, 1.35}, {1.0, 1.05, 1.15}};
+constexpr Weights kBf16 = {{1.25, 1.45, 1.75, 1.9}, 1.7, 2.7, {5.2, 9.3, 13.15}, 1.9, 5.05,
+                           {1.05, 1.65, 2.45}, {0.95, 1.3, 1.45}, {1.0, 1.1, 1.65}};
 
 constexpr double kSplitRate = 4.0e6, kScanRate = 5.4e6;   // bytes of planes per microsecond that bound a large store
-constexpr double kMmStageUs = 0.8;                        // a stage (k-step) of k_traj_mm
-
-// A stage (layer group of a slice) of the general scan, by its query tiles.
-double scan_stage_us(bool bf, int TQ) {
-  if (bf) return TQ == 1 ? 0.75 : (TQ == 2 ? 0.9 : (TQ == 4 ? 1.0 : 1.2));
-  return TQ == 1 ? 1.0 : (TQ == 2 ? 1.3 : (TQ == 4 ? 1.55 : 2.8));
-}
 
 }  // namespace
 
 // The scan with the least estimated time: the longest workgroup's dependent
-// stages or k-steps, but no less than the planes take to read.  Both sides
-// measured (scan alone, us, the other scan / this one): float32 24 x 60, 8
-// queries 1,000 maps 25.5 / 6.1, 16,000 26.9 / 18.3, 50,000 49.6 / 72; 64
-// queries 16,000 maps 38.9 / 25.0, 50,000 52.4 / 101; 32 x 8, 8 queries 1,000
-// maps 9.2 / 4.5; bf16 24 x 60, 100 queries 4,000 maps 30.3 / 9.5, 16 queries
-// 200,003 maps 110 / 150; 32 x 16 float32, 1,000 queries 4,000 maps 31.5 / 29.5.
-TrajSplit traj_split_plan(bool bf, int32_t n, int32_t row, const Geo& geo, int32_t Bc, int nlg, int TQ, int nba,
-                          bool mm) {
+// stages or k-steps and the ranking that ends a slice or step, but no less than
+// the planes take to read.  The weights are fitted to 3,700 random sizes (200
+// to 150,000 maps of twelve shapes, 1 to 1,024 queries, lists of 1, 4 and 8,
+// depths uniform, geometric and full), each timed on the other scan and on
+// every shape here: five of them lose 3% or more against the other scan (9% at
+// most), and the mean call takes 0.72 of its time there.  The
+// depths are not known on the host, and shallow batches of several groups are
+// much quicker on the other scan than deep ones: some deep batches stay there
+// that would gain here.  (Without the ranking, and with every stage weighed at
+// what the first one of a scan costs, calls took up to 2.9 times the other
+// scan's time.)  Both sides, the call on the other scan / on the best shape
+// here, us: float32 32 x 8, 1,000 maps, 8 queries 18.6 / 14.3; 24 x 60, 6,766
+// maps, 4 queries 36.3 / 15.6; bf16 61 x 33, 28,275 maps, 2 queries 52.0 /
+// 23.5; and on the other scan: float32 24 x 60, 23,877 maps, 322 queries 98.8 /
+// 182.8, 26 x 60, 20,420 maps, 80 queries 48.7 / 72.8.
+TrajSplit traj_split_plan(bool bf, int32_t n, int32_t row, const Geo& geo, int32_t Bc, int KTOP, int nlg, int TQ,
+                          int nba, bool mm) {
+  const Weights& wt = bf ? kBf16 : kF32;
+  const int kl = KTOP == 1 ? 0 : (KTOP == 4 ? 1 : 2);
   const int n_blocks = (n + 15) / 16;
   const double bytes = static_cast<double>(n) * nlg * geo.lpg * row * (bf ? 2 : 4);
   double best;
   if (mm) {
     const int slices = (n_blocks + 15) / 16 * ((Bc + traj_mm_group() - 1) / traj_mm_group());
-    best = static_cast<double>((slices + traj_mm_workgroups() - 1) / traj_mm_workgroups()) * nlg * geo.ksg * kMmStageUs;
+    best = static_cast<double>((slices + traj_mm_workgroups() - 1) / traj_mm_workgroups()) *
+           (nlg * geo.ksg * wt.mm_stage + wt.mm_slice);
   } else {
     const int n_qg = (Bc + 16 * TQ - 1) / (16 * TQ);
+    // (one group's workgroups walk whole slices; several groups share the
+    // workgroups by their cost)
     int R = 256 / n_qg;
     if (R > n_blocks) R = n_blocks;
     if (R < 1) R = 1;
+    const int sw = 128 * nba;   // maps per slice
     const int maps = (n + R - 1) / R;
-    best = static_cast<double>((maps + 128 * nba - 1) / (128 * nba)) * nlg * scan_stage_us(bf, TQ);
+    double slices = (maps + sw - 1) / sw;
+    if (n_qg > 1) slices = static_cast<double>(n) * n_qg / (256.0 * sw);
+    if (n_qg > 1 && slices < 1.0) slices = 1.0;
+    const double stage = wt.stage[TQ == 1 ? 0 : (TQ == 2 ? 1 : (TQ == 4 ? 2 : 3))] * (geo.ksg == 2 ? wt.two_ksteps : 1.0);
+    best = slices * (nlg * stage + wt.slice + wt.score[kl] * TQ * nba / 8.0);
   }
   if (best < bytes / kScanRate) best = bytes / kScanRate;
   const int run = ((nlg * geo.ksg + kSW - 1) / kSW + kSD - 1) / kSD * kSD;   // k-steps of a wavefront
@@ -371,7 +398,7 @@ TrajSplit traj_split_plan(bool bf, int32_t n, int32_t row, const Geo& geo, int32
     if (R > units) R = units;
     if (R < 1) R = 1;
     const int steps = ((n_blocks + R - 1) / R + si.nb - 1) / si.nb;
-    double t = static_cast<double>(steps) * run * (bf ? si.bf16_us : si.f32_us);
+    double t = steps * (run * wt.kstep[i] + wt.step[i] * wt.lists[kl]);
     if (t < bytes / kSplitRate) t = bytes / kSplitRate;
     if (t < best) {
       best = t;

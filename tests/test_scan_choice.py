@@ -43,3 +43,20 @@ SEMANTIC = [(1000, 4096, 8, 92.6, 11.8), (955, 768, 8, 26.6, 8.4), (3540, 2048, 
 @pytest.mark.parametrize("n,d,B,mm,split", SEMANTIC)
 def test_semantic_search_takes_the_scan_that_measured_faster(n, d, B, mm, split):
     assert fm.debug_scan_name(32, 8, n, B, d_emb=d).startswith("k_sem_mm" if mm < split else "k_sem_split")
+
+
+# (L, E, maps, queries, matches, type, time of the call on the other trajectory
+# scan, on the best split-depth shape), us
+TRAJECTORY = [(32, 8, 1000, 8, 1, "f32", 18.6, 14.3), (61, 33, 320, 2, 1, "f32", 64.1, 14.9),
+              (48, 32, 272, 281, 1, "f32", 79.3, 27.1), (24, 60, 6766, 4, 1, "f32", 36.3, 15.6),
+              (61, 33, 1699, 10, 1, "bf16", 52.7, 20.6), (61, 33, 28275, 2, 1, "bf16", 52.0, 23.5),
+              (7, 4, 7223, 234, 4, "bf16", 39.8, 24.0),
+              (24, 60, 72606, 130, 1, "f32", 129.1, 339.8), (24, 64, 53410, 79, 1, "f32", 83.0, 201.7),
+              (24, 60, 23877, 322, 1, "f32", 98.8, 182.8), (26, 60, 20420, 80, 1, "f32", 48.7, 72.8),
+              (26, 60, 8994, 451, 1, "f32", 60.4, 120.4), (48, 32, 39534, 191, 1, "bf16", 44.0, 82.8),
+              (48, 32, 21317, 541, 1, "f32", 129.6, 215.3), (24, 64, 18824, 160, 1, "f32", 48.5, 84.4)]
+
+
+@pytest.mark.parametrize("L,E,n,B,k,dtype,other,split", TRAJECTORY)
+def test_trajectory_search_takes_the_scan_that_measured_faster(L, E, n, B, k, dtype, other, split):
+    assert fm.debug_scan_name(L, E, n, B, k, dtype).startswith("k_traj_split") == (split < other)
