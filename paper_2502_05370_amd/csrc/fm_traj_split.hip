@@ -341,6 +341,7 @@ constexpr Weights kF32 = {{0.8, 1.05, 1.2, 1.4}, 1.5, 2.4, {3.0, 9.6, 10.2}, 0.0
 constexpr Weights kBf16 = {{1.25, 1.45, 1.75, 1.9}, 1.7, 2.7, {5.2, 9.3, 13.15}, 1.9, 5.05,
                            {1.05, 1.65, 2.45}, {0.95, 1.3, 1.45}, {1.0, 1.1, 1.65}};
 
+constexpr double kMostSlices = 3.0;   // of the other scan, with which the split-depth scan competes
 constexpr double kSplitRate = 4.0e6, kScanRate = 5.4e6;   // bytes of planes per microsecond that bound a large store
 
 }  // namespace
@@ -350,28 +351,31 @@ constexpr double kSplitRate = 4.0e6, kScanRate = 5.4e6;   // bytes of planes per
 // the planes take to read.  The weights are fitted to 3,700 random sizes (200
 // to 150,000 maps of twelve shapes, 1 to 1,024 queries, lists of 1, 4 and 8,
 // depths uniform, geometric and full), each timed on the other scan and on
-// every shape here: five of them lose 3% or more against the other scan (9% at
-// most), and the mean call takes 0.72 of its time there.  The
-// depths are not known on the host, and shallow batches of several groups are
-// much quicker on the other scan than deep ones: some deep batches stay there
-// that would gain here.  (Without the ranking, and with every stage weighed at
-// what the first one of a scan costs, calls took up to 2.9 times the other
-// scan's time.)  Both sides, the call on the other scan / on the best shape
-// here, us: float32 32 x 8, 1,000 maps, 8 queries 18.6 / 14.3; 24 x 60, 6,766
-// maps, 4 queries 36.3 / 15.6; bf16 61 x 33, 28,275 maps, 2 queries 52.0 /
-// 23.5; and on the other scan: float32 24 x 60, 23,877 maps, 322 queries 98.8 /
-// 182.8, 26 x 60, 20,420 maps, 80 queries 48.7 / 72.8.
+// every shape here: four of them lose 3% or more against the other scan (6% at
+// most), and the mean call takes 0.72 of its time there.  The depths are not
+// known on the host, and shallow batches of several groups are much quicker on
+// the other scan than deep ones: some deep batches stay there that would gain
+// here.  A scan whose workgroups walk more than three slices keeps its loads and
+// stages overlapped, which the weights do not show, and stays (of 2,698 sizes
+// where a shape here was 3% quicker, 10 lie there; float32 16 x 20, 79,793 maps,
+// top-8 of 870 queries 323 us there, 569 here).  (Without the ranking, and with
+// every stage weighed at what the first one of a scan costs, calls took up to
+// 2.9 times the other scan's time.)  Both sides, the call on the other scan / on
+// the best shape here, us: float32 32 x 8, 1,000 maps, 8 queries 18.6 / 14.3; 24
+// x 60, 6,766 maps, 4 queries 36.3 / 15.6; bf16 61 x 33, 28,275 maps, 2 queries
+// 52.0 / 23.5; and on the other scan: float32 24 x 60, 23,877 maps, 322 queries
+// 98.8 / 182.8, 26 x 60, 20,420 maps, 80 queries 48.7 / 72.8.
 TrajSplit traj_split_plan(bool bf, int32_t n, int32_t row, const Geo& geo, int32_t Bc, int KTOP, int nlg, int TQ,
                           int nba, bool mm) {
   const Weights& wt = bf ? kBf16 : kF32;
   const int kl = KTOP == 1 ? 0 : (KTOP == 4 ? 1 : 2);
   const int n_blocks = (n + 15) / 16;
   const double bytes = static_cast<double>(n) * nlg * geo.lpg * row * (bf ? 2 : 4);
-  double best;
+  double best, slices;
   if (mm) {
-    const int slices = (n_blocks + 15) / 16 * ((Bc + traj_mm_group() - 1) / traj_mm_group());
-    best = static_cast<double>((slices + traj_mm_workgroups() - 1) / traj_mm_workgroups()) *
-           (nlg * geo.ksg * wt.mm_stage + wt.mm_slice);
+    const int all = (n_blocks + 15) / 16 * ((Bc + traj_mm_group() - 1) / traj_mm_group());
+    slices = (all + traj_mm_workgroups() - 1) / traj_mm_workgroups();
+    best = slices * (nlg * geo.ksg * wt.mm_stage + wt.mm_slice);
   } else {
     const int n_qg = (Bc + 16 * TQ - 1) / (16 * TQ);
     // (one group's workgroups walk whole slices; several groups share the
@@ -381,7 +385,7 @@ TrajSplit traj_split_plan(bool bf, int32_t n, int32_t row, const Geo& geo, int32
     if (R < 1) R = 1;
     const int sw = 128 * nba;   // maps per slice
     const int maps = (n + R - 1) / R;
-    double slices = (maps + sw - 1) / sw;
+    slices = (maps + sw - 1) / sw;
     if (n_qg > 1) slices = static_cast<double>(n) * n_qg / (256.0 * sw);
     if (n_qg > 1 && slices < 1.0) slices = 1.0;
     const double stage = wt.stage[TQ == 1 ? 0 : (TQ == 2 ? 1 : (TQ == 4 ? 2 : 3))] * (geo.ksg == 2 ? wt.two_ksteps : 1.0);
@@ -390,6 +394,7 @@ TrajSplit traj_split_plan(bool bf, int32_t n, int32_t row, const Geo& geo, int32
   if (best < bytes / kScanRate) best = bytes / kScanRate;
   const int run = ((nlg * geo.ksg + kSW - 1) / kSW + kSD - 1) / kSD * kSD;   // k-steps of a wavefront
   TrajSplit p;
+  if (slices > kMostSlices) return p;
   for (int i = 0; i < static_cast<int>(sizeof(kShapes) / sizeof(kShapes[0])); ++i) {
     const ShapeInfo& si = kShapes[i];
     const int n_qg = (Bc + 16 * si.tq - 1) / (16 * si.tq);

@@ -54,7 +54,8 @@ TRAJECTORY = [(32, 8, 1000, 8, 1, "f32", 18.6, 14.3), (61, 33, 320, 2, 1, "f32",
               (24, 60, 72606, 130, 1, "f32", 129.1, 339.8), (24, 64, 53410, 79, 1, "f32", 83.0, 201.7),
               (24, 60, 23877, 322, 1, "f32", 98.8, 182.8), (26, 60, 20420, 80, 1, "f32", 48.7, 72.8),
               (26, 60, 8994, 451, 1, "f32", 60.4, 120.4), (48, 32, 39534, 191, 1, "bf16", 44.0, 82.8),
-              (48, 32, 21317, 541, 1, "f32", 129.6, 215.3), (24, 64, 18824, 160, 1, "f32", 48.5, 84.4)]
+              (48, 32, 21317, 541, 1, "f32", 129.6, 215.3), (24, 64, 18824, 160, 1, "f32", 48.5, 84.4),
+              (16, 20, 79793, 870, 8, "f32", 323.0, 569.0), (32, 16, 79793, 870, 8, "f32", 342.0, 574.0)]
 
 
 @pytest.mark.parametrize("L,E,n,B,k,dtype,other,split", TRAJECTORY)
