@@ -360,8 +360,10 @@ fm_status fm_debug_scores(const fm_store* store, const void* q, const int32_t* d
  * names the dense form (fm_debug_scores).  A name, then for a kernel of several
  * shapes a space and the shape: "k_traj_scan", "k_traj_mm", "k_traj_split RxC"
  * (blocks of 16 maps by tiles of 16 queries), "k_sem_scan", "k_sem_mm Q"
- * (queries per group), "k_sem_split RxC".  A constant string; NULL for sizes
- * that the match calls refuse.  Runs on the host, without a GPU. */
+ * (queries per group), "k_sem_split RxC"; "k_traj_scan floors" is k_traj_scan
+ * with the ranking floors that a query group's workgroups share.  A constant
+ * string; NULL for sizes that the match calls refuse.  Runs on the host,
+ * without a GPU. */
 const char* fm_debug_scan_name(int32_t L, int32_t E, int32_t d_emb, fm_dtype map_dtype, int32_t n,
                                int32_t max_depth, int32_t B, int32_t k);
 

@@ -85,6 +85,7 @@ struct ScanArgs {
   Workspace ws;
   float* dbg;         // optional dense scores [B][n]
   int32_t vec16;      // dense rows written 16 bytes at a time: n % 4 == 0, an aligned buffer
+  int32_t floors;     // ranking floors (the FL form)
 };
 
 // Stable sort of the batch by depth, deepest first.  A query's position is
@@ -819,9 +820,8 @@ __global__ void __launch_bounds__(512) k_traj_scan(ScanArgs a) {
         // the largest such bound.  Without it some lane of a wavefront
         // improves its own list at nearly every score: ranking took half of a
         // shallow group's time (200,000 Phi-shaped float32 maps, 512 queries,
-        // top-4: 266 -> 205 us with the shares below).  FL serves launches of
-        // two or more query groups; the 256 workgroups of a single group see
-        // too few slices each, and the exchange cost them up to 20%.
+        // top-4: 266 -> 205 us with the shares below).  FL serves the launches
+        // of floors_pay.
 #pragma unroll
         for (int t = 0; t < TQ; ++t) {
           const int r = 16 * t + c;
@@ -1079,10 +1079,8 @@ constexpr int tq_limit(bool bf, int ksg, int ktop) {
 template <bool BF, int KSG, int KTOP, int TQ, bool DBG>
 hipError_t scan_tq1(const ScanArgs& a, size_t lds, hipStream_t st) {
   if constexpr (TQ <= tq_limit(BF, KSG, KTOP)) {
-    // (more than one group: the batch fills the largest group size, unless
-    // LDS holds it down)
     if constexpr (!DBG && TQ == tq_limit(BF, KSG, KTOP))
-      if (a.n_qg > 1) return scan_launch<BF, TQ, scan_nba(TQ, KSG, BF), KSG, KTOP, false, true>(a, lds, st);
+      if (a.floors != 0) return scan_launch<BF, TQ, scan_nba(TQ, KSG, BF), KSG, KTOP, false, true>(a, lds, st);
     return scan_launch<BF, TQ, scan_nba(TQ, KSG, BF), KSG, KTOP, DBG, false>(a, lds, st);
   }
   return hipErrorInvalidValue;
@@ -1117,10 +1115,24 @@ size_t traj_qrows_bytes(int L, int E, fm_dtype dt, int b_pad) {
 
 namespace {
 
+// Ranking floors serve launches of two or more query groups (of the largest
+// group size) whose workgroups walk enough slices: the floor rises with the
+// logarithm of the maps seen, its exchange and its test cost every slice.  By
+// slices per workgroup (with floors / without, the call): up to 1, 1.00 .. 1.06;
+// 1 to 4, 0.86 .. 1.10 and 1.02 on average; above 4 (one k-step per layer
+// group), 0.54 .. 1.02; above 8 (two k-steps: a slice has twice the products for
+// the same ranking), 0.71 .. 1.06 and 0.95 on average.
+bool floors_pay(int32_t n, int32_t Bc, int KTOP, bool bf, const Geo& geo, int TQ) {
+  const int64_t n_qg = (Bc + 16 * TQ - 1) / (16 * TQ);
+  const int64_t slice = 128 * scan_nba(TQ, geo.ksg, bf);
+  return n_qg > 1 && TQ == tq_limit(bf, geo.ksg, KTOP) && n * n_qg >= 256 * slice * (geo.ksg == 1 ? 4 : 8);
+}
+
 // The scan that a launch of Bc queries takes.
 struct TrajPlan {
   int TQ = 1;         // query tiles per group of k_traj_scan
   bool mm = false;    // k_traj_mm, unless the split-depth scan is taken
+  bool floors = false;   // k_traj_scan with ranking floors
   TrajSplit split;
   bool split_taken() const { return split.shape >= 0; }
 };
@@ -1133,6 +1145,7 @@ TrajPlan traj_plan(bool bf, int32_t n, int32_t row, const Geo& geo, int32_t Bc, 
   // smaller query groups when the staged planes of one would not fit the ring
   while (p.TQ > 1 && scan_lds(bf, p.TQ, geo.ksg, KTOP, max_depth) > kScanLds) p.TQ /= 2;
   p.mm = traj_mm_fits(bf, KTOP, n, Bc, max_depth, nlg, geo.ksg);
+  p.floors = !dense && floors_pay(n, Bc, KTOP, bf, geo, p.TQ);
   // the split-depth scan where it is the faster one (fm_traj_split.hip; it
   // has no dense form)
   if (!dense) p.split = traj_split_plan(bf, n, row, geo, Bc, KTOP, nlg, p.TQ, scan_nba(p.TQ, geo.ksg, bf), p.mm);
@@ -1145,7 +1158,7 @@ const char* traj_scan_name(bool bf, int32_t E, int32_t n, int32_t Bc, int32_t k,
   const int KTOP = k <= 1 ? 1 : (k <= 4 ? 4 : 8);
   const TrajPlan p = traj_plan(bf, n, row_elems(E), geometry(E), Bc, KTOP, max_depth, k == 0);
   if (p.split_taken()) return traj_split_name(p.split);
-  return p.mm ? "k_traj_mm" : "k_traj_scan";
+  return p.mm ? "k_traj_mm" : (p.floors ? "k_traj_scan floors" : "k_traj_scan");
 }
 
 hipError_t launch_match_trajectory(const StoreView& s, const void* q, const int32_t* depth, int32_t max_depth,
@@ -1279,6 +1292,7 @@ hipError_t launch_match_trajectory(const StoreView& s, const void* q, const int3
     a.ws = ws;
     a.dbg = dbg_scores != nullptr ? dbg_scores + static_cast<int64_t>(b0) * s.n : nullptr;
     a.vec16 = s.n % 4 == 0 && reinterpret_cast<uintptr_t>(a.dbg) % 16 == 0;
+    a.floors = pl.floors ? 1 : 0;
     if (dbg_scores != nullptr) {
       // same arithmetic as the match kernels, plus the dense score stores
       err = bf ? scan_ksg<true, 1, true>(geo.ksg, TQ, a, lds, st) : scan_ksg<false, 1, true>(geo.ksg, TQ, a, lds, st);

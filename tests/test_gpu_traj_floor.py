@@ -17,7 +17,8 @@ pytestmark = pytest.mark.gpu
 @pytest.mark.parametrize("copies", [True, False])
 @pytest.mark.parametrize("dtype,E,k,B,n", [("f32", 16, 4, 1000, 33001), ("f32", 8, 8, 600, 20011),
                                            ("f32", 60, 1, 600, 20003), ("bf16", 60, 8, 600, 20003),
-                                           ("bf16", 16, 3, 600, 33007)])
+                                           ("bf16", 16, 3, 600, 33007), ("f32", 60, 1, 600, 60003),
+                                           ("bf16", 60, 8, 1000, 40003), ("bf16", 16, 3, 1000, 40007)])
 def test_floors_keep_every_match(dtype, E, k, B, n, copies):
     import paper_2502_05370_amd as fm
     L = 5

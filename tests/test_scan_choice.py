@@ -10,7 +10,7 @@ def test_names_follow_the_sizes():
     assert name(32, 8, 1000, 8) == "k_traj_split 1x1"
     assert name(24, 60, 1000000, 512, 1, "bf16") == "k_traj_mm"
     assert name(24, 60, 50000, 64) == "k_traj_scan"
-    assert name(32, 16, 200000, 512, 4) == "k_traj_scan"
+    assert name(32, 16, 200000, 512, 4).startswith("k_traj_scan")
     assert name(32, 8, 1000, 8, d_emb=4096) == "k_sem_split 1x1"
     assert name(24, 60, 1000000, 512, d_emb=2048) == "k_sem_mm 256"
     assert name(32, 8, 100000, 100, d_emb=4096) == "k_sem_mm 128"
@@ -61,3 +61,24 @@ TRAJECTORY = [(32, 8, 1000, 8, 1, "f32", 18.6, 14.3), (61, 33, 320, 2, 1, "f32",
 @pytest.mark.parametrize("L,E,n,B,k,dtype,other,split", TRAJECTORY)
 def test_trajectory_search_takes_the_scan_that_measured_faster(L, E, n, B, k, dtype, other, split):
     assert fm.debug_scan_name(L, E, n, B, k, dtype).startswith("k_traj_split") == (split < other)
+
+
+# (L, E, maps, queries, matches, type, time of the call with ranking floors, without), us
+FLOORS = [(32, 16, 84064, 689, 1, "f32", 148.4, 160.9), (12, 12, 56666, 695, 8, "f32", 237.3, 261.2),
+          (32, 8, 187879, 306, 8, "f32", 213.9, 262.5), (24, 60, 62658, 1007, 1, "f32", 266.0, 327.1),
+          (24, 60, 102912, 433, 8, "bf16", 243.6, 251.5), (12, 40, 163634, 793, 8, "bf16", 426.2, 583.6),
+          (32, 8, 30452, 142, 1, "f32", 30.6, 29.1), (12, 12, 112923, 127, 8, "bf16", 97.5, 89.8),
+          (24, 60, 40658, 205, 1, "f32", 84.9, 78.8), (16, 20, 91654, 44, 8, "f32", 76.7, 70.7),
+          (24, 60, 34393, 512, 1, "f32", 126.7, 118.3), (32, 8, 46879, 160, 8, "bf16", 74.3, 67.3)]
+
+
+@pytest.mark.parametrize("L,E,n,B,k,dtype,with_floors,without", FLOORS)
+def test_ranking_floors_serve_the_launches_that_measured_faster(L, E, n, B, k, dtype, with_floors, without):
+    assert fm.debug_scan_name(L, E, n, B, k, dtype) == ("k_traj_scan floors" if with_floors < without else "k_traj_scan")
+
+
+# the sizes of the GPU test of the floors that reach them
+@pytest.mark.parametrize("dtype,E,k,B,n", [("f32", 16, 4, 1000, 33001), ("f32", 8, 8, 600, 20011), ("f32", 60, 1, 600, 60003),
+                                           ("bf16", 60, 8, 1000, 40003), ("bf16", 16, 3, 1000, 40007)])
+def test_floor_test_reaches_the_floors(dtype, E, k, B, n):
+    assert fm.debug_scan_name(5, E, n, B, k, dtype) == "k_traj_scan floors"
