@@ -1241,12 +1241,14 @@ hipError_t launch_match_trajectory(const StoreView& s, const void* q, const int3
     if (G < n_qg) G = n_qg;
     pa.n_qg = n_qg;
     pa.G = G;
-    // slice epilogue vs stage cost in the sharing of the workgroups among the
-    // groups, per query tile and map block: the least total over the
-    // Phi-shaped batches with depths from both laws (weights 0 .. 300 tried:
-    // top-1 154 us at the best against 203 at the worst, top-4 218 .. 271,
-    // top-8 339 .. 520)
-    pa.epi16 = TQ * scan_nba(TQ, geo.ksg, bf) * (KTOP == 1 ? 2 : KTOP == 4 ? 5 : 8);
+    // Slice epilogue vs stage cost in the sharing of the workgroups among the
+    // groups, per query tile and map block, in sixteenths of a stage.  Over 171
+    // random sizes of two or more groups (weights 0 .. 12 tried) these are within
+    // 2.2% of the best on average for every shape; lower ones give shallow groups
+    // too few workgroups (61 x 33 float32, 133,686 maps, 283 queries of geometric
+    // depths: weight 2 367 us, 4 301).
+    const int epi = KTOP == 1 ? (geo.ksg == 1 ? 2 : 4) : KTOP == 4 ? (geo.ksg == 1 ? 5 : 8) : 12;
+    pa.epi16 = TQ * scan_nba(TQ, geo.ksg, bf) * epi;
     const dim3 pgrid(b_pad / 16, nlg + 4);
     if (bf) hipLaunchKernelGGL(k_traj_prep<true>, pgrid, dim3(kThreads), 0, st, pa);
     else hipLaunchKernelGGL(k_traj_prep<false>, pgrid, dim3(kThreads), 0, st, pa);
