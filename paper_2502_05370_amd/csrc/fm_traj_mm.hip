@@ -1,5 +1,6 @@
 // Trajectory-based expert map search (Section 4.2.2, Eq. 5), top-1 form for
-// bfloat16 stores and batches of more than 128 queries (96 on larger stores).
+// bfloat16 stores and batches of more than 128 queries (96 on larger stores,
+// see traj_mm_fits).
 //
 // The batch is the contraction of the depth-sorted query prefixes with the
 // stored maps' prefixes, layer group by layer group, on
@@ -580,15 +581,18 @@ hipError_t traj_mm_launch(const TrajMmArgs& a, hipStream_t st) {
 
 int traj_mm_workgroups() { return 256; }
 
-// A band is 256 queries; half a band still pays where each workgroup has a
-// slice and a half or more to walk, since the general scan runs 8 tiles of 128
-// queries at one wavefront row per tile (us, general / this: 200,003 x 24 x 60
-// 100 queries 149.5 / 145.2, 800,000 128 queries 473 / 447, 300,000 x 32 x 8
-// 100 queries 69.4 / 62.3, 100,000 x 32 x 16 120 queries 46.0 / 40.1; but
-// 50,000 x 24 x 60 100 queries 50.7 / 54.4, and 200,003 70 queries 143.0 /
-// 144.8).
+// A band is 256 queries.  Half a band (97 to 128 queries: one group of
+// k_traj_scan) still pays where each workgroup has enough slices to walk: one
+// and a half, or three where a layer group is two k-steps.  k_traj_scan / this,
+// the call, us: one k-step, of 148 sizes from 98,304 maps on 0.70 .. 0.98 of
+// k_traj_scan's time (105,953 x 32 x 16, 109 queries 42.6 / 39.1; 293,509 x 32 x
+// 8, 115 queries 64.9 / 56.0); two k-steps, 98,304 to 196,607 maps 0.80 .. 1.06,
+// slower for 35 of 53 (111,618 x 24 x 60, 123 queries 82.6 / 87.4), above 0.86 ..
+// 1.03 and even on average with depths up to L (200,003 x 24 x 60, 100 queries
+// of depths below L 151 / 147: this scan does not walk the last layer).  Fewer
+// queries were not better here: 200,003 x 24 x 60, 70 queries 143.0 / 144.8.
 bool traj_mm_fits(bool bf, int KTOP, int32_t n, int32_t Bc, int32_t max_depth, int nlg, int ksg) {
-  const bool wide = Bc > 128 || (Bc > 96 && n >= 16 * kSB * traj_mm_workgroups() * 3 / 2);
+  const bool wide = Bc > 128 || (Bc > 96 && n >= 16 * kSB * traj_mm_workgroups() * 3 / 2 * ksg);
   return bf && KTOP == 1 && wide && max_depth <= kRows && nlg * ksg >= 2 && (ksg == 1 || ksg == 2);
 }
 

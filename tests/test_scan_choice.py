@@ -82,3 +82,15 @@ def test_ranking_floors_serve_the_launches_that_measured_faster(L, E, n, B, k, d
                                            ("bf16", 60, 8, 1000, 40003), ("bf16", 16, 3, 1000, 40007)])
 def test_floor_test_reaches_the_floors(dtype, E, k, B, n):
     assert fm.debug_scan_name(5, E, n, B, k, dtype) == "k_traj_scan floors"
+
+
+# (L, E, maps, queries, time of the call on k_traj_scan, on k_traj_mm), us: bf16,
+# one match, half a band of k_traj_mm
+HALF_BAND = [(32, 16, 105953, 109, 42.6, 39.1), (32, 8, 185776, 114, 45.9, 41.5), (32, 8, 293509, 115, 64.9, 56.0),
+             (16, 20, 145156, 119, 57.7, 48.5), (24, 60, 215644, 97, 147.7, 127.1), (24, 64, 309628, 114, 201.4, 197.7),
+             (24, 60, 111618, 123, 82.6, 87.4), (24, 60, 159606, 113, 116.1, 120.4), (24, 64, 122243, 112, 88.3, 91.4)]
+
+
+@pytest.mark.parametrize("L,E,n,B,scan,mm", HALF_BAND)
+def test_half_a_band_takes_the_scan_that_measured_faster(L, E, n, B, scan, mm):
+    assert fm.debug_scan_name(L, E, n, B, 1, "bf16") == ("k_traj_mm" if mm < scan else "k_traj_scan")
