@@ -294,9 +294,12 @@ __global__ void __launch_bounds__(256) k_merge_select(SelArgs a, MergeArgs m) {
   const int lo = a.lb[b], hi = a.le[b];
   const float rq = m.rq != nullptr ? m.rq[pos] : 1.0f;
   for (int r = threadIdx.x + 256; r < nr; r += 256) t.merge(plist + static_cast<int64_t>(r) * KTOP);
-  // (a wavefront past the lists has nothing to merge)
+  // (A wavefront past the lists has nothing to merge.  The loops stay loops: a
+  // merge of two lists of 8 is over a hundred instructions, and nine copies of
+  // it cost more to fetch than they save, with one query of 8,861 x 256, top-8
+  // the call 27.4 us unrolled, 25.0 as loops.)
   if (wv * kWave < nr) {
-#pragma unroll
+#pragma unroll 1
     for (int off = 1; off < kWave; off <<= 1) {
       uint64_t o[KTOP];
 #pragma unroll
@@ -312,7 +315,7 @@ __global__ void __launch_bounds__(256) k_merge_select(SelArgs a, MergeArgs m) {
   // every wavefront merges the four lists for itself (the same result)
 #pragma unroll
   for (int jj = 0; jj < KTOP; ++jj) t.v[jj] = wlist[0][jj];
-#pragma unroll
+#pragma unroll 1
   for (int ww = 1; ww < 4; ++ww)
     if (ww * kWave < nr) t.merge(wlist[ww]);
   if (lane == 0) {
