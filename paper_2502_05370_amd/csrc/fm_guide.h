@@ -24,33 +24,40 @@ __device__ __forceinline__ float stored_prob(const GuideView& v, int y, int l, i
   return bf16_to_f32(static_cast<const uint16_t*>(v.planes)[off]);
 }
 
-// p of expert j at layer l for one query: idx_b / score_b are its k matches
-// in ranking order (idx_b[0] is a valid store index; -1 entries are skipped).
-// The rows of all matches load together: one after the other in the sum's
-// order, each waited for the one before (top-8 rows of 100 queries, merge and
-// selection 13.7 -> 10.0 us; the blended selection of 512 x 24 rows of 60 experts
-// 24.6 -> 21.9 us).
-__device__ __forceinline__ double guide_prob(const GuideView& v, const int32_t* idx_b, const float* score_b, int k,
-                                             int blend, int l, int j) {
-  if (blend != FM_BLEND_SCORE) return static_cast<double>(stored_prob(v, idx_b[0], l, j));
+// The k matches of one query in ranking order (-1: none, or past the store).
+struct Matches {
   int32_t y[kMaxK];
-  float p[kMaxK], sc[kMaxK];
+  float score[kMaxK];
+};
+__device__ __forceinline__ Matches load_matches(int32_t n, const int32_t* idx_b, const float* score_b, int k) {
+  Matches m;
 #pragma unroll
   for (int i = 0; i < kMaxK; ++i) {
-    y[i] = i < k ? idx_b[i] : -1;
-    sc[i] = i < k ? score_b[i] : 0.0f;
-    if (y[i] >= v.n) y[i] = -1;
+    m.y[i] = i < k ? idx_b[i] : -1;
+    m.score[i] = i < k ? score_b[i] : 0.0f;
+    if (m.y[i] >= n) m.y[i] = -1;
   }
+  return m;
+}
+
+// p of expert j at layer l for one query from its matches (y[0] is a valid
+// store index; -1 entries are skipped).  The rows of all matches load together:
+// one after the other in the sum's order, each waited for the one before (top-8
+// rows of 100 queries, merge and selection 13.7 -> 10.0 us; the blended
+// selection of 512 x 24 rows of 60 experts 24.6 -> 21.9 us).
+__device__ __forceinline__ double guide_prob(const GuideView& v, const Matches& m, int blend, int l, int j) {
+  if (blend != FM_BLEND_SCORE) return static_cast<double>(stored_prob(v, m.y[0], l, j));
+  float p[kMaxK];
 #pragma unroll
-  for (int i = 0; i < kMaxK; ++i) p[i] = y[i] >= 0 ? stored_prob(v, y[i], l, j) : 0.0f;
+  for (int i = 0; i < kMaxK; ++i) p[i] = m.y[i] >= 0 ? stored_prob(v, m.y[i], l, j) : 0.0f;
   bool any_pos = false;
 #pragma unroll
-  for (int i = 0; i < kMaxK; ++i) any_pos = any_pos || (y[i] >= 0 && sc[i] > 0.0f);
+  for (int i = 0; i < kMaxK; ++i) any_pos = any_pos || (m.y[i] >= 0 && m.score[i] > 0.0f);
   double num = 0.0, den = 0.0;
 #pragma unroll
   for (int i = 0; i < kMaxK; ++i) {
-    if (y[i] < 0) continue;
-    const double s = static_cast<double>(sc[i]);
+    if (m.y[i] < 0) continue;
+    const double s = static_cast<double>(m.score[i]);
     const double wgt = any_pos ? (s > 0.0 ? s : 0.0) : 1.0;
     num = __dadd_rn(num, __dmul_rn(wgt, static_cast<double>(p[i])));
     den = __dadd_rn(den, wgt);

@@ -50,8 +50,9 @@ __device__ __forceinline__ uint32_t ord_value(float s) {
 }  // namespace
 
 // Place the candidates by counting: a candidate's place is the number of keys
-// above its own (keys are distinct), read from LDS as broadcasts; OWN
-// candidates per thread.
+// above its own (keys are distinct), read from LDS as broadcasts, eight in
+// flight (64 queries of about 700 candidates of 24 x 60: the call 22.6 us, with
+// four 27.5); OWN candidates per thread.
 template <int OWN>
 __device__ __forceinline__ void place_by_count(const PriArgs& a, const uint64_t* keys, int N, int b) {
   const int tid = threadIdx.x;
@@ -62,7 +63,7 @@ __device__ __forceinline__ void place_by_count(const PriArgs& a, const uint64_t*
     mine[u] = tid + u * kPriThreads < N ? keys[tid + u * kPriThreads] : 0ull;
     rank[u] = 0;
   }
-#pragma unroll 4
+#pragma unroll 8
   for (int i = 0; i < N; ++i) {
     const uint64_t x = keys[i];
 #pragma unroll
@@ -128,10 +129,13 @@ __global__ void __launch_bounds__(kPriThreads) k_priority(PriArgs a) {
       cand[first[l] + __popcll(bits & ((1ull << lane) - 1ull))] = static_cast<uint16_t>(l * kMaxE + lane);
   }
   __syncthreads();
+  // (the matches are read once: read again for every candidate, they came
+  // before its probability each time)
+  const Matches m = load_matches(a.gv.n, idx_b, score_b, a.k);
   for (int i = tid; i < N; i += kPriThreads) {
     const int l = cand[i] / kMaxE;
     const int j = cand[i] % kMaxE;
-    const double p = guide_prob(a.gv, idx_b, score_b, a.k, a.blend, l, j);
+    const double p = guide_prob(a.gv, m, a.blend, l, j);
     double v;
     if (a.kind == FM_PRI_PREFETCH) {
       v = __ddiv_rn(p, static_cast<double>(l - lnow));

@@ -146,7 +146,11 @@ __device__ __forceinline__ void select_row(const SelArgs& a, bool in, int b, int
   // them discards the value)
   const GuideView gv{a.planes, a.plane_elems, a.n, a.row, a.dtype};
   const bool has = j < a.E && y0 >= 0 && y0 < a.n;
-  const double p = has ? guide_prob(gv, idx_b, score_b, a.k, a.blend, l, j) : 0.0;
+  double p = 0.0;
+  if (has) {
+    const Matches m = load_matches(a.n, idx_b, score_b, a.k);
+    p = guide_prob(gv, m, a.blend, l, j);
+  }
 
   bool live = in && l >= lo && l < hi && y0 >= 0;
   if (live && y0 >= a.n) {
