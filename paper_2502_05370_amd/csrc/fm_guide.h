@@ -40,13 +40,12 @@ __device__ __forceinline__ Matches load_matches(int32_t n, const int32_t* idx_b,
   return m;
 }
 
-// p of expert j at layer l for one query from its matches (y[0] is a valid
-// store index; -1 entries are skipped).  The rows of all matches load together:
+// Blended p of expert j at layer l for one query from its matches (-1 entries
+// are skipped, y[0] is none of them).  The rows of all matches load together:
 // one after the other in the sum's order, each waited for the one before (top-8
 // rows of 100 queries, merge and selection 13.7 -> 10.0 us; the blended
 // selection of 512 x 24 rows of 60 experts 24.6 -> 21.9 us).
-__device__ __forceinline__ double guide_prob(const GuideView& v, const Matches& m, int blend, int l, int j) {
-  if (blend != FM_BLEND_SCORE) return static_cast<double>(stored_prob(v, m.y[0], l, j));
+__device__ __forceinline__ double blended_prob(const GuideView& v, const Matches& m, int l, int j) {
   float p[kMaxK];
 #pragma unroll
   for (int i = 0; i < kMaxK; ++i) p[i] = m.y[i] >= 0 ? stored_prob(v, m.y[i], l, j) : 0.0f;

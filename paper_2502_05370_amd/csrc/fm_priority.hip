@@ -129,22 +129,28 @@ __global__ void __launch_bounds__(kPriThreads) k_priority(PriArgs a) {
       cand[first[l] + __popcll(bits & ((1ull << lane) - 1ull))] = static_cast<uint16_t>(l * kMaxE + lane);
   }
   __syncthreads();
-  // (the matches are read once: read again for every candidate, they came
-  // before its probability each time)
-  const Matches m = load_matches(a.gv.n, idx_b, score_b, a.k);
-  for (int i = tid; i < N; i += kPriThreads) {
-    const int l = cand[i] / kMaxE;
-    const int j = cand[i] % kMaxE;
-    const double p = guide_prob(a.gv, m, a.blend, l, j);
-    double v;
-    if (a.kind == FM_PRI_PREFETCH) {
-      v = __ddiv_rn(p, static_cast<double>(l - lnow));
-    } else {
-      const double prod = __dmul_rn(p, static_cast<double>(a.freq[l * a.E + j]));
-      v = __ddiv_rn(1.0, prod);
+  auto fill = [&](auto prob) __attribute__((always_inline)) {
+    for (int i = tid; i < N; i += kPriThreads) {
+      const int l = cand[i] / kMaxE;
+      const int j = cand[i] % kMaxE;
+      const double p = prob(l, j);
+      double v;
+      if (a.kind == FM_PRI_PREFETCH) {
+        v = __ddiv_rn(p, static_cast<double>(l - lnow));
+      } else {
+        const double prod = __dmul_rn(p, static_cast<double>(a.freq[l * a.E + j]));
+        v = __ddiv_rn(1.0, prod);
+      }
+      const uint32_t e = static_cast<uint32_t>(l * a.E + j);
+      keys[i] = (static_cast<uint64_t>(ord_value(static_cast<float>(v))) << 32) | static_cast<uint32_t>(~e);
     }
-    const uint32_t e = static_cast<uint32_t>(l * a.E + j);
-    keys[i] = (static_cast<uint64_t>(ord_value(static_cast<float>(v))) << 32) | static_cast<uint32_t>(~e);
+  };
+  // (a blend's matches are read once, not again before every candidate)
+  if (a.blend == FM_BLEND_SCORE) {
+    const Matches m = load_matches(a.gv.n, idx_b, score_b, a.k);
+    fill([&](int l, int j) { return blended_prob(a.gv, m, l, j); });
+  } else {
+    fill([&](int l, int j) { return static_cast<double>(stored_prob(a.gv, y0, l, j)); });
   }
   // the places past the candidates
   for (int i = N + tid; i < a.cap; i += kPriThreads) {

@@ -148,8 +148,8 @@ __device__ __forceinline__ void select_row(const SelArgs& a, bool in, int b, int
   const bool has = j < a.E && y0 >= 0 && y0 < a.n;
   double p = 0.0;
   if (has) {
-    const Matches m = load_matches(a.n, idx_b, score_b, a.k);
-    p = guide_prob(gv, m, a.blend, l, j);
+    p = a.blend == FM_BLEND_SCORE ? blended_prob(gv, load_matches(a.n, idx_b, score_b, a.k), l, j)
+                                  : static_cast<double>(stored_prob(gv, y0, l, j));
   }
 
   bool live = in && l >= lo && l < hi && y0 >= 0;
@@ -298,12 +298,14 @@ __global__ void __launch_bounds__(256) k_merge_select(SelArgs a, MergeArgs m) {
   const int lo = a.lb[b], hi = a.le[b];
   const float rq = m.rq != nullptr ? m.rq[pos] : 1.0f;
   for (int r = threadIdx.x + 256; r < nr; r += 256) t.merge(plist + static_cast<int64_t>(r) * KTOP);
-  // (A wavefront past the lists has nothing to merge.  The loops stay loops: a
-  // merge of two lists of 8 is over a hundred instructions, and nine copies of
-  // it cost more to fetch than they save, with one query of 8,861 x 256, top-8
-  // the call 27.4 us unrolled, 25.0 as loops.)
+  // (A wavefront past the lists has nothing to merge.  The merges of longer lists
+  // stay loops: two lists of 8 take over a hundred instructions, and nine copies
+  // of them cost more to fetch than they save, with one query of 8,861 x 256,
+  // top-8 the call 27.4 us unrolled, 25.0 as loops; those of one match are 0.4 us
+  // quicker unrolled.)
+  constexpr int kRounds = KTOP == 1 ? 6 : 1, kMerges = KTOP == 1 ? 3 : 1;
   if (wv * kWave < nr) {
-#pragma unroll 1
+#pragma unroll kRounds
     for (int off = 1; off < kWave; off <<= 1) {
       uint64_t o[KTOP];
 #pragma unroll
@@ -319,7 +321,7 @@ __global__ void __launch_bounds__(256) k_merge_select(SelArgs a, MergeArgs m) {
   // every wavefront merges the four lists for itself (the same result)
 #pragma unroll
   for (int jj = 0; jj < KTOP; ++jj) t.v[jj] = wlist[0][jj];
-#pragma unroll 1
+#pragma unroll kMerges
   for (int ww = 1; ww < 4; ++ww)
     if (ww * kWave < nr) t.merge(wlist[ww]);
   if (lane == 0) {
