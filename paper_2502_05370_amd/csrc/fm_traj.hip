@@ -1118,14 +1118,16 @@ namespace {
 // Ranking floors serve launches of two or more query groups (of the largest
 // group size) whose workgroups walk enough slices: the floor rises with the
 // logarithm of the maps seen, its exchange and its test cost every slice.  By
-// slices per workgroup (with floors / without, the call): up to 1, 1.00 .. 1.06;
-// 1 to 4, 0.86 .. 1.10 and 1.02 on average; above 4 (one k-step per layer
-// group), 0.54 .. 1.02; above 8 (two k-steps: a slice has twice the products for
-// the same ranking), 0.71 .. 1.06 and 0.95 on average.
-bool floors_pay(int32_t n, int32_t Bc, int KTOP, bool bf, const Geo& geo, int TQ) {
+// slices per workgroup (with floors / without, the call): up to 1, 1.00 .. 1.10;
+// 1 to 4, 0.86 .. 1.10 and 1.02 on average, but with one or two layer groups in
+// all, where ranking is most of a slice, 0.84 .. 1.04 from 2.5 on; above 4 (one
+// k-step per layer group), 0.50 .. 1.02; above 8 (two k-steps: a slice has twice
+// the products for the same ranking), 0.60 .. 1.06 and 0.95 on average.
+bool floors_pay(int32_t n, int32_t Bc, int KTOP, bool bf, const Geo& geo, int nlg, int TQ) {
   const int64_t n_qg = (Bc + 16 * TQ - 1) / (16 * TQ);
   const int64_t slice = 128 * scan_nba(TQ, geo.ksg, bf);
-  return n_qg > 1 && TQ == tq_limit(bf, geo.ksg, KTOP) && n * n_qg >= 256 * slice * (geo.ksg == 1 ? 4 : 8);
+  const int64_t halves = geo.ksg == 2 ? 16 : (nlg <= 2 ? 5 : 8);   // least half slices per workgroup
+  return n_qg > 1 && TQ == tq_limit(bf, geo.ksg, KTOP) && 2 * n * n_qg >= 256 * slice * halves;
 }
 
 // The scan that a launch of Bc queries takes.
@@ -1145,7 +1147,7 @@ TrajPlan traj_plan(bool bf, int32_t n, int32_t row, const Geo& geo, int32_t Bc, 
   // smaller query groups when the staged planes of one would not fit the ring
   while (p.TQ > 1 && scan_lds(bf, p.TQ, geo.ksg, KTOP, max_depth) > kScanLds) p.TQ /= 2;
   p.mm = traj_mm_fits(bf, KTOP, n, Bc, max_depth, nlg, geo.ksg);
-  p.floors = !dense && floors_pay(n, Bc, KTOP, bf, geo, p.TQ);
+  p.floors = !dense && floors_pay(n, Bc, KTOP, bf, geo, nlg, p.TQ);
   // the split-depth scan where it is the faster one (fm_traj_split.hip; it
   // has no dense form)
   if (!dense) p.split = traj_split_plan(bf, n, row, geo, Bc, KTOP, nlg, p.TQ, scan_nba(p.TQ, geo.ksg, bf), p.mm);
