@@ -583,16 +583,24 @@ int traj_mm_workgroups() { return 256; }
 
 // A band is 256 queries.  Half a band (97 to 128 queries: one group of
 // k_traj_scan) still pays where each workgroup has enough slices to walk: one
-// and a half, or three where a layer group is two k-steps.  k_traj_scan / this,
+// and a half, or where a layer group is two k-steps three, or one slice fewer
+// than k_traj_scan, whose even shares of the maps begin anywhere in a block and
+// spill into one more slice when they nearly fill the last.  k_traj_scan / this,
 // the call, us: one k-step, of 148 sizes from 98,304 maps on 0.70 .. 0.98 of
 // k_traj_scan's time (105,953 x 32 x 16, 109 queries 42.6 / 39.1; 293,509 x 32 x
-// 8, 115 queries 64.9 / 56.0); two k-steps, 98,304 to 196,607 maps 0.80 .. 1.06,
-// slower for 35 of 53 (111,618 x 24 x 60, 123 queries 82.6 / 87.4), above 0.86 ..
-// 1.03 and even on average with depths up to L (200,003 x 24 x 60, 100 queries
-// of depths below L 151 / 147: this scan does not walk the last layer).  Fewer
-// queries were not better here: 200,003 x 24 x 60, 70 queries 143.0 / 144.8.
+// 8, 115 queries 64.9 / 56.0); two k-steps, 98,304 to 196,607 maps 1.00 .. 1.06
+// (111,618 x 24 x 60, 123 queries 82.6 / 87.4), but 0.80 .. 0.87 where
+// k_traj_scan spills (193,368 x 24 x 64, 118 queries 152.6 / 128.5); above that
+// 0.86 .. 1.03, even on average with depths up to L and 3% quicker below L
+// (200,003 x 24 x 60, 100 queries 151 / 147: this scan does not walk the last
+// layer).  Fewer queries were not better here: 200,003 x 24 x 60, 70 queries
+// 143.0 / 144.8.
 bool traj_mm_fits(bool bf, int KTOP, int32_t n, int32_t Bc, int32_t max_depth, int nlg, int ksg) {
-  const bool wide = Bc > 128 || (Bc > 96 && n >= 16 * kSB * traj_mm_workgroups() * 3 / 2 * ksg);
+  const int G = traj_mm_workgroups();
+  const int scan_slices = ((((n + G - 1) / G) + 30) / 16 + 15) / 16;
+  const int slices = ((n + 15) / 16 + kSB * G - 1) / (kSB * G);
+  const bool half = n >= 16 * kSB * G * 3 / 2 && (ksg == 1 || n >= 16 * kSB * G * 3 || slices < scan_slices);
+  const bool wide = Bc > 128 || (Bc > 96 && half);
   return bf && KTOP == 1 && wide && max_depth <= kRows && nlg * ksg >= 2 && (ksg == 1 || ksg == 2);
 }
 

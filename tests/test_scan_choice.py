@@ -69,7 +69,9 @@ FLOORS = [(32, 16, 84064, 689, 1, "f32", 148.4, 160.9), (12, 12, 56666, 695, 8, 
           (24, 60, 102912, 433, 8, "bf16", 243.6, 251.5), (12, 40, 163634, 793, 8, "bf16", 426.2, 583.6),
           (32, 8, 30452, 142, 1, "f32", 30.6, 29.1), (12, 12, 112923, 127, 8, "bf16", 97.5, 89.8),
           (24, 60, 40658, 205, 1, "f32", 84.9, 78.8), (16, 20, 91654, 44, 8, "f32", 76.7, 70.7),
-          (24, 60, 34393, 512, 1, "f32", 126.7, 118.3), (32, 8, 46879, 160, 8, "bf16", 74.3, 67.3)]
+          (24, 60, 34393, 512, 1, "f32", 126.7, 118.3), (32, 8, 46879, 160, 8, "bf16", 74.3, 67.3),
+          (1, 16, 56892, 428, 1, "f32", 31.1, 37.4), (2, 8, 100741, 144, 1, "f32", 34.3, 40.3),
+          (2, 8, 32409, 167, 1, "f32", 25.8, 23.6)]
 
 
 @pytest.mark.parametrize("L,E,n,B,k,dtype,with_floors,without", FLOORS)
@@ -88,6 +90,7 @@ def test_floor_test_reaches_the_floors(dtype, E, k, B, n):
 # one match, half a band of k_traj_mm
 HALF_BAND = [(32, 16, 105953, 109, 42.6, 39.1), (32, 8, 185776, 114, 45.9, 41.5), (32, 8, 293509, 115, 64.9, 56.0),
              (16, 20, 145156, 119, 57.7, 48.5), (24, 60, 215644, 97, 147.7, 127.1), (24, 64, 309628, 114, 201.4, 197.7),
+             (24, 60, 195589, 107, 144.6, 108.9), (24, 64, 127247, 126, 113.2, 93.9), (24, 64, 193368, 118, 152.6, 128.5),
              (24, 60, 111618, 123, 82.6, 87.4), (24, 60, 159606, 113, 116.1, 120.4), (24, 64, 122243, 112, 88.3, 91.4)]
 
 
