@@ -1,8 +1,7 @@
 """GPU: the match-and-select calls (fm_match_semantic_select,
 fm_match_trajectory_select) give exactly what a match call followed by
 fm_select_prefetch on the same rows gives (matches, scores, sets, counts),
-for every scan kernel they can follow (semantic top-1 and top-k, trajectory
-bf16 top-1 and the general scan with per-group list counts), FIXED and
+for every scan kernel they can follow (the named cases say which), FIXED and
 DYNAMIC thresholds, the similarity blend and a batch beyond one launch; the
 separate calls are themselves checked against the oracle in the other
 parity tests, and one case here is checked against it directly."""
@@ -60,21 +59,29 @@ def _assert_identical(sep, fus):
 
 
 CASES = [
-    # (name, config, n, B_traj, B_sem, k)
-    ("traj_f32_general_scan", 2, 3001, 64, 0, 1),
-    ("traj_f32_groups_top4_blend", 4, 4003, 300, 0, 4),
-    ("traj_bf16_mm_and_sem_mm", 5, 2501, 300, 200, 1),
-    ("traj_bf16_small_batch", 5, 1500, 70, 20, 1),
-    ("sem_top8", 3, 2050, 0, 40, 8),
-    ("traj_f32_top8", 1, 1000, 37, 0, 8),
+    # (name, config, n, B_traj, B_sem, k, trajectory scan, semantic scan)
+    ("traj_f32_general_scan", 2, 30011, 64, 0, 1, "k_traj_scan", None),
+    ("traj_f32_groups_top4_blend", 4, 20011, 300, 0, 4, "k_traj_scan", None),
+    ("traj_f32_floors_top8", 1, 60013, 600, 0, 8, "k_traj_scan floors", None),
+    ("traj_f32_split_depth", 2, 3001, 64, 0, 1, "k_traj_split", None),
+    ("traj_bf16_mm_and_sem_mm", 5, 30011, 300, 200, 1, "k_traj_mm", "k_sem_mm"),
+    ("traj_bf16_small_batch", 5, 1500, 70, 20, 1, "k_traj_split", "k_sem_split"),
+    ("sem_top8", 3, 2050, 0, 40, 8, None, "k_sem_scan"),
+    ("traj_f32_top8", 1, 1000, 37, 0, 8, "k_traj_split", None),
 ]
 
 
 @pytest.mark.parametrize("case", CASES, ids=[c[0] for c in CASES])
 def test_fused_equals_separate(case):
-    name, cfg, n, bt, bs, k = case
+    import paper_2502_05370_amd as fm
+    name, cfg, n, bt, bs, k, traj, sem = case
     print(f"{name}: config {cfg} n={n} B_traj={bt} B_sem={bs} k={k}", flush=True)
     s = dataclasses.replace(synth.spec(cfg).scaled(n=n, B_traj=bt, B_sem=bs), k=k)
+    if traj:
+        got = fm.debug_scan_name(s.L, s.E, n, bt, k, s.map_dtype)
+        assert got == traj if traj.startswith("k_traj_scan") else got.startswith(traj)
+    if sem:
+        assert fm.debug_scan_name(s.L, s.E, n, bs, k, s.map_dtype, d_emb=s.d_emb).startswith(sem)
     a = synth.generate(s)
     sep, fus, flags = _run_both(s, a)
     assert flags == 0
@@ -92,10 +99,15 @@ def test_fused_threshold_modes_and_blend(mode, blend):
 
 def test_fused_batch_beyond_one_launch():
     """1030 semantic and 1100 trajectory queries: a launch of 1024 on the
-    top-1 scans, then the rest (6 semantic queries on the 128-query shape, 76
-    trajectory queries on the general scan); fused equals separate, and both
-    halves match the oracle on every row."""
-    s = synth.spec(5).scaled(n=1500, B_traj=1100, B_sem=1030)
+    top-1 scans, then the rest (6 semantic and 76 trajectory queries) on the
+    split scans; fused equals separate, and both halves match the oracle on
+    every row."""
+    import paper_2502_05370_amd as fm
+    s = synth.spec(5).scaled(n=8011, B_traj=1100, B_sem=1030)
+    assert fm.debug_scan_name(s.L, s.E, s.n, 1100, 1, s.map_dtype) == "k_traj_mm"
+    assert fm.debug_scan_name(s.L, s.E, s.n, 76, 1, s.map_dtype).startswith("k_traj_split")
+    assert fm.debug_scan_name(s.L, s.E, s.n, 1030, 1, s.map_dtype, d_emb=s.d_emb) == "k_sem_mm 256"
+    assert fm.debug_scan_name(s.L, s.E, s.n, 6, 1, s.map_dtype, d_emb=s.d_emb).startswith("k_sem_split")
     print(f"config 5 n={s.n} B_traj={s.B_traj} B_sem={s.B_sem}", flush=True)
     a = synth.generate(s)
     sep, fus, flags = _run_both(s, a)

@@ -1,8 +1,9 @@
-"""GPU parity of the split-k semantic scan at the edges of its shapes: 16-query
-tiles, steps of 1 or 4 blocks of 16 maps, k-steps that do not divide evenly
-over the wavefronts (d = 128: four k-steps for eight), one match and lists of
-4 and 8, with zero, scaled, infinite and NaN queries and zero and NaN stored
-embeddings, against the CPU oracle on the same arrays.  Index and score rules
+"""GPU parity of the split-k semantic scan at the edges of its five shapes:
+16-query tiles, steps of 1 or 4 blocks of 16 maps, k-steps that do not divide
+evenly over the wavefronts (d = 128: four k-steps for eight), one match and the
+dense form, with zero, scaled, infinite and NaN queries and zero and NaN stored
+embeddings, against the CPU oracle on the same arrays; and lists of 4 and 8 of
+the same inputs, which k_sem_scan serves.  Index and score rules
 as for every match (parity.compare_topk)."""
 import numpy as np
 import pytest
@@ -21,7 +22,7 @@ def _embeddings(rng, n, d):
 
 @pytest.mark.parametrize("n,d,B", [(1, 128, 1), (15, 128, 5), (17, 384, 16), (250, 4096, 17), (1003, 1152, 33),
                                    (1003, 256, 65), (4100, 2048, 8), (4100, 640, 129), (333, 1024, 300),
-                                   (9001, 1024, 70)])
+                                   (9001, 1024, 70), (1052, 4096, 450), (12007, 2048, 100)])
 def test_split_scan_matches_oracle(n, d, B):
     import paper_2502_05370_amd as fm
     rng = np.random.default_rng(n + d + B)

@@ -67,6 +67,8 @@ def test_deep_non_finite_values_stay_out_of_shallower_tiles(E, L, n, B, dtype):
     whose deepest query ends before that layer group keeps its finite scores,
     whatever deeper tiles share its workgroup."""
     import paper_2502_05370_amd as fm
+    for k in (1, 4):
+        assert fm.debug_scan_name(L, E, n, B, k, dtype).startswith("k_traj_split 2")
     rng = np.random.default_rng(E + n)
     maps = rng.dirichlet(np.ones(E), size=(n, L)).astype(np.float32)
     lpg = 32 // E if E >= 8 and 32 % E == 0 else 1

@@ -70,8 +70,8 @@ FLOORS = [(32, 16, 84064, 689, 1, "f32", 148.4, 160.9), (12, 12, 56666, 695, 8, 
           (32, 8, 30452, 142, 1, "f32", 30.6, 29.1), (12, 12, 112923, 127, 8, "bf16", 97.5, 89.8),
           (24, 60, 40658, 205, 1, "f32", 84.9, 78.8), (16, 20, 91654, 44, 8, "f32", 76.7, 70.7),
           (24, 60, 34393, 512, 1, "f32", 126.7, 118.3), (32, 8, 46879, 160, 8, "bf16", 74.3, 67.3),
-          (1, 16, 56892, 428, 1, "f32", 31.1, 37.4), (2, 8, 100741, 144, 1, "f32", 34.3, 40.3),
-          (2, 8, 32409, 167, 1, "f32", 25.8, 23.6)]
+          (1, 16, 56892, 428, 1, "bf16", 31.1, 37.4), (2, 8, 100741, 144, 1, "f32", 34.3, 40.3),
+          (2, 8, 32409, 167, 1, "bf16", 25.8, 23.6)]
 
 
 @pytest.mark.parametrize("L,E,n,B,k,dtype,with_floors,without", FLOORS)
@@ -97,3 +97,17 @@ HALF_BAND = [(32, 16, 105953, 109, 42.6, 39.1), (32, 8, 185776, 114, 45.9, 41.5)
 @pytest.mark.parametrize("L,E,n,B,scan,mm", HALF_BAND)
 def test_half_a_band_takes_the_scan_that_measured_faster(L, E, n, B, scan, mm):
     assert fm.debug_scan_name(L, E, n, B, 1, "bf16") == ("k_traj_mm" if mm < scan else "k_traj_scan")
+
+
+# the sizes of the GPU tests of the split scans, and the shapes that they reach
+@pytest.mark.parametrize("shape,n,d,B", [("1x1", 250, 4096, 17), ("4x1", 4100, 2048, 8), ("4x2", 1052, 4096, 450),
+                                         ("4x4", 4100, 640, 129), ("4x8", 12007, 2048, 100)])
+def test_semantic_split_test_reaches_every_shape(shape, n, d, B):
+    assert fm.debug_scan_name(2, 4, n, B, d_emb=d) == f"k_sem_split {shape}"
+
+
+@pytest.mark.parametrize("dtype", ["f32", "bf16"])
+@pytest.mark.parametrize("shape,E,L,n,B", [("1x1", 60, 24, 1003, 33), ("2x2", 60, 6, 4100, 200), ("2x4", 8, 32, 4100, 100)])
+@pytest.mark.parametrize("k", [1, 3, 8])
+def test_trajectory_split_test_reaches_every_shape(shape, E, L, n, B, k, dtype):
+    assert fm.debug_scan_name(L, E, n, B, k, dtype) == f"k_traj_split {shape}"
