@@ -97,19 +97,17 @@ __device__ __forceinline__ float key_score(uint64_t key) {
   return key == 0 ? -__builtin_inff() : unord_score(static_cast<uint32_t>(key >> 32));
 }
 
-// The jj-th match of a merged list whose keys rank by dot / |x|, given rq =
-// 1/|q|: the factor is positive and leaves the order alone.  rq = 0 is a zero
-// query (every dot 0, so the list is the lowest indices) or one with an
-// infinity, whose every cosine is NaN: its dots are infinite or NaN, and its
-// matches are the lowest indices of the n stored ones.
-__device__ __forceinline__ void scale_match(uint64_t key, uint64_t key0, float rq, int32_t n, int jj, int32_t& idx,
-                                            float& score) {
+// The match of a key that ranks by dot / |x|, given rq = 1/|q|: the factor is
+// positive and leaves the order alone.  rq = 0 is a zero query (every dot 0, so
+// the key holds the lowest index) or one with an infinity, whose every cosine is
+// NaN: its dots are infinite or NaN, and its match is the lowest index.
+__device__ __forceinline__ void scale_match(uint64_t key, float rq, int32_t& idx, float& score) {
+  const float top = key_score(key);
   idx = key_index(key);
-  score = key == 0 ? -__builtin_inff() : key_score(key) * rq;
-  const float top = key_score(key0);
-  if (key0 != 0 && rq == 0.0f && !(__builtin_fabsf(top) < __builtin_inff())) {
-    idx = jj < n ? jj : -1;
-    score = jj < n ? __builtin_nanf("") : -__builtin_inff();
+  score = key == 0 ? top : top * rq;
+  if (key != 0 && rq == 0.0f && !(__builtin_fabsf(top) < __builtin_inff())) {
+    idx = 0;
+    score = __builtin_nanf("");
   }
 }
 

@@ -85,12 +85,11 @@ DedupScratch carve_dedup_scratch(void* base, int32_t cap, int32_t n_max);
 Workspace carve_workspace(void* base);
 size_t traj_qrows_bytes(int L, int E, fm_dtype dt, int b_pad);
 // partial holds R lists per position; with rgrp set, position pos merges only
-// the first rgrp[pos / qg] of them.  With rq set, the lists rank by
-// dot / |x| and the scores written are that times rq[pos] = 1/|q| (n: the
-// store's size).
+// the first rgrp[pos / qg] of them.  With rq set (top-1 lists), they rank by
+// dot / |x| and the scores written are that times rq[pos] = 1/|q|.
 hipError_t launch_finalize(const uint64_t* partial, const int32_t* perm, int32_t B, int32_t R, int32_t k, int KTOP,
                            int32_t* idx_out, float* score_out, hipStream_t st, const int32_t* rgrp = nullptr,
-                           int32_t qg = 0, const float* rq = nullptr, int32_t n = 0);
+                           int32_t qg = 0, const float* rq = nullptr);
 
 // Caller-provided events bracketing the next scan launches on this thread
 // (both null when unset); see fm_debug_scan_events.

@@ -266,7 +266,7 @@ struct MergeArgs {
   int32_t qg;                // positions per query group
   int32_t* idx_out;          // [B][k]
   float* score_out;          // [B][k]
-  const float* rq;           // 1/|q| per position, for lists that rank by dot / |x| (NULL: the keys hold the scores)
+  const float* rq;           // top-1 lists that rank by dot / |x|: 1/|q| per position (NULL: the keys hold the scores)
 };
 
 template <int KTOP, int SW>
@@ -296,7 +296,7 @@ __global__ void __launch_bounds__(256) k_merge_select(SelArgs a, MergeArgs m) {
     for (int jj = 0; jj < KTOP; ++jj) t.v[jj] = static_cast<int>(threadIdx.x) < nr ? first[jj] : 0ull;
   }
   const int lo = a.lb[b], hi = a.le[b];
-  const float rq = m.rq != nullptr ? m.rq[pos] : 1.0f;
+  const float rq = KTOP == 1 && m.rq != nullptr ? m.rq[pos] : 1.0f;
   for (int r = threadIdx.x + 256; r < nr; r += 256) t.merge(plist + static_cast<int64_t>(r) * KTOP);
   // (A wavefront past the lists has nothing to merge.  The merges of longer lists
   // stay loops: two lists of 8 take over a hundred instructions, and nine copies
@@ -331,7 +331,8 @@ __global__ void __launch_bounds__(256) k_merge_select(SelArgs a, MergeArgs m) {
       const uint64_t key = jj < KTOP ? t.v[jj < KTOP ? jj : 0] : 0ull;
       int32_t y = key_index(key);
       float sc = key_score(key);
-      if (m.rq != nullptr) scale_match(key, t.v[0], rq, a.n, jj, y, sc);
+      if constexpr (KTOP == 1)
+        if (m.rq != nullptr) scale_match(key, rq, y, sc);
       midx[wv][jj] = y;
       mscore[wv][jj] = sc;
       if (blockIdx.y == 0 && wv == 0) {

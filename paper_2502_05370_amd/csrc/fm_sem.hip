@@ -30,9 +30,9 @@ namespace {
 
 struct SemPrepArgs {
   const uint16_t* q;   // [B][d] bf16
-  int32_t B, d, b_pad;
-  uint16_t* qst;       // tiled [b_pad][d]
-  float* rq;           // [b_pad]
+  int32_t B, d;
+  uint16_t* qst;       // tiled [positions][d]
+  float* rq;           // [positions]
 };
 
 struct SemArgs {
@@ -65,9 +65,11 @@ __device__ __forceinline__ SemPos next_sem_pos(const SemPos& p, int nkc, int ns)
 }  // namespace
 
 // One workgroup per query position, so that a row's loads are in flight
-// together (a wavefront per row took a load round trip per 512 dimensions:
-// 256 queries of d = 4096 9.1 -> 5.2 us): the row is copied 8 dimensions (16
-// bytes) at a time into its tile slots; positions past B get zero rows.
+// together (a wavefront per row took a load round trip per 512 dimensions: the
+// kernel, 256 queries of d = 4096, 9.1 -> 6.4 us; the whole call is 2 us quicker
+// at d = 4096 with 8 or 100 queries and the same up to d = 1024): the row is
+// copied 8 dimensions (16 bytes) at a time into its tile slots; positions past B
+// get zero rows.
 __global__ void __launch_bounds__(256) k_sem_prep(SemPrepArgs a) {
   __shared__ double part[4];
   const int lane = threadIdx.x % kWave;
@@ -487,7 +489,6 @@ hipError_t launch_match_semantic(const StoreView& s, const void* q, int32_t B, i
     pa.q = static_cast<const uint16_t*>(q) + static_cast<int64_t>(b0) * s.d_emb;
     pa.B = Bc;
     pa.d = s.d_emb;
-    pa.b_pad = b_pad;
     pa.qst = static_cast<uint16_t*>(ws.qrows);
     pa.rq = ws.rq;
     hipError_t err = hipSuccess;
@@ -505,7 +506,7 @@ hipError_t launch_match_semantic(const StoreView& s, const void* q, int32_t B, i
                                       idx_out + static_cast<int64_t>(b0) * k, score_out + static_cast<int64_t>(b0) * k,
                                       fuse->at(b0, s.L), st, ws.rq)
                 : launch_finalize(ws.partial, nullptr, Bc, sp.R, k, KTOP, idx_out + static_cast<int64_t>(b0) * k,
-                                  score_out + static_cast<int64_t>(b0) * k, st, nullptr, 0, ws.rq, s.n);
+                                  score_out + static_cast<int64_t>(b0) * k, st, nullptr, 0, ws.rq);
       if (err != hipSuccess) return err;
       continue;
     }

@@ -37,9 +37,9 @@
 // streaming hints on the map loads and a k-step rotation per workgroup were
 // each within 3% and are not used.
 //
-// TQ = 1 and 2 (up to 32 queries) read the caller's rows themselves and
-// spread the query norms over the group's workgroups, so the search is two
-// launches; larger groups read the tiles staged by k_sem_prep (a caller's row
+// TQ = 1 and 2 (groups of up to 32 queries, however many groups) read the
+// caller's rows themselves and spread the query norms over the group's
+// workgroups, so the search is two launches; larger groups read the tiles staged by k_sem_prep (a caller's row
 // gives 64 contiguous bytes per k-step, and rows a multiple of 4 KB apart lie
 // on one memory channel, which 64 and more rows feel).
 #include "fm_device.h"
@@ -54,7 +54,7 @@ struct SplitArgs {
   const float* xnorm;    // [cap] |x|
   const uint16_t* q;     // RAW: [B][d] rows; else staged tiles
   float* rq;             // [b_pad] 1/|q| (RAW: written here)
-  uint64_t* partial;     // [b_pad][R][KTOP]
+  uint64_t* partial;     // [b_pad][R]: one packed key per (query, workgroup of its group)
   // dense form: the scores [B][n], or w_self * score + w_mix * mix
   float* dbg;
   const float* mix;
@@ -67,15 +67,12 @@ struct SplitArgs {
   int32_t grid;
 };
 
-constexpr int KTOP = 1;   // matches kept per query
-
 template <int W, int NB, int TQ>
 struct SplitShape {
   static constexpr int TC0 = W * NB * TQ <= 128 ? TQ : 128 / (W * NB);   // query tiles per reduction phase (128 KB of LDS)
   static constexpr int TC = TC0 < W ? TC0 : W;
   static constexpr int PAIRS = NB * TC;
   static constexpr int PH = TQ / TC;                  // phases
-  static constexpr int LISTS = PH;                    // query tiles a wavefront keeps lists of
   static_assert(TQ % TC == 0 && W % TC == 0, "a wavefront sums one query tile per phase");
 };
 
@@ -116,9 +113,9 @@ __global__ void __launch_bounds__(W * 64) __attribute__((amdgpu_waves_per_eu(W /
   const int g0 = qgrp * QG;
   if (!active) return;
 
-  TopK<KTOP> best[PH];
+  uint64_t best[PH];   // best key of this lane's query of each phase
 #pragma unroll
-  for (int p = 0; p < PH; ++p) best[p].clear();
+  for (int p = 0; p < PH; ++p) best[p] = 0;
 
   // this wavefront's k-steps [k0, k1), padded to a multiple of D (the padding
   // loads read zeros)
@@ -289,8 +286,10 @@ __global__ void __launch_bounds__(W * 64) __attribute__((amdgpu_waves_per_eu(W /
             }
           } else {
 #pragma unroll
-            for (int r = 0; r < 4; ++r)
-              if (y0 + r < a.n) best[ph].push(split_key(sum[r] * rx[r], y0 + r));
+            for (int r = 0; r < 4; ++r) {
+              const uint64_t key = y0 + r < a.n ? split_key(sum[r] * rx[r], y0 + r) : 0ull;
+              best[ph] = key > best[ph] ? key : best[ph];
+            }
           }
         }
       }
@@ -306,32 +305,26 @@ __global__ void __launch_bounds__(W * 64) __attribute__((amdgpu_waves_per_eu(W /
   if constexpr (DENSE) return;   // no lists
 
   // merge: the four lane groups of a query, then the W / TC wavefronts of its tile
-  uint64_t* mbuf = reinterpret_cast<uint64_t*>(smem);   // [W][PH][16][KTOP]
+  uint64_t* mbuf = reinterpret_cast<uint64_t*>(smem);   // [W][PH][16]
 #pragma unroll
   for (int ph = 0; ph < PH; ++ph) {
 #pragma unroll
     for (int m = 16; m <= 32; m <<= 1) {
-      uint64_t o[KTOP];
-#pragma unroll
-      for (int jj = 0; jj < KTOP; ++jj) o[jj] = shfl_xor_u64(best[ph].v[jj], m);
-      best[ph].merge(o);
+      const uint64_t o = shfl_xor_u64(best[ph], m);
+      best[ph] = o > best[ph] ? o : best[ph];
     }
-    if (g == 0) {
-#pragma unroll
-      for (int jj = 0; jj < KTOP; ++jj) mbuf[((w * PH + ph) * 16 + c) * KTOP + jj] = best[ph].v[jj];
-    }
+    if (g == 0) mbuf[(w * PH + ph) * 16 + c] = best[ph];
   }
   __syncthreads();
   for (int r = tid; r < QG; r += W * kWave) {
     const int t = r / 16;
-    const int ph = t / TC;
-    TopK<KTOP> m;
-    m.clear();
+    uint64_t m = 0;
 #pragma unroll
-    for (int ww = 0; ww < W / TC; ++ww) m.merge(mbuf + (((t % TC + ww * TC) * PH + ph) * 16 + r % 16) * KTOP);
-    uint64_t* out = a.partial + (static_cast<int64_t>(g0 + r) * a.R + rr) * KTOP;
-#pragma unroll
-    for (int jj = 0; jj < KTOP; ++jj) out[jj] = m.v[jj];
+    for (int ww = 0; ww < W / TC; ++ww) {
+      const uint64_t o = mbuf[((t % TC + ww * TC) * PH + t / TC) * 16 + r % 16];
+      m = o > m ? o : m;
+    }
+    a.partial[static_cast<int64_t>(g0 + r) * a.R + rr] = m;
   }
 }
 
@@ -341,7 +334,7 @@ template <int W, int NB, int TQ, int D, bool RAW, bool DENSE = false>
 hipError_t split_launch(const SplitArgs& a, hipStream_t st) {
   using S = SplitShape<W, NB, TQ>;
   constexpr size_t red = static_cast<size_t>(W) * S::PAIRS * 1024;
-  constexpr size_t mrg = static_cast<size_t>(W) * S::PH * 16 * KTOP * 8;
+  constexpr size_t mrg = static_cast<size_t>(W) * S::PH * 16 * 8;
   constexpr size_t lds = red > mrg ? red : mrg;
   static_assert(lds <= 160 * 1024, "LDS");
   static_assert(!(RAW && DENSE), "the dense form reads 1/|q| in the scan");

@@ -72,7 +72,7 @@ __global__ void __launch_bounds__(256) k_insert_maps(const T* __restrict__ src, 
   // The running sums in layer order, one lane per layer (each adds the layers
   // up to its own, read from LDS as broadcasts, so that the square roots and
   // divisions of the layers run side by side: one thread doing all of them
-  // took most of the kernel, 256 maps of 32 x 8 18.6 -> 7.0 us).
+  // took most of the kernel, 256 maps of 32 x 8 18.6 -> 14.2 us).
   if (threadIdx.x < static_cast<unsigned>(L)) {
     double cum = 0.0;
     for (int l = 0; l <= static_cast<int>(threadIdx.x); ++l) cum += sq[l];

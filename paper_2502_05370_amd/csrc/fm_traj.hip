@@ -965,7 +965,7 @@ template <int KTOP>
 __global__ void __launch_bounds__(256) k_finalize(const uint64_t* __restrict__ partial, const int32_t* __restrict__ perm,
                                                   int32_t B, int32_t R, int32_t k, int32_t* __restrict__ idx_out,
                                                   float* __restrict__ score_out, const int32_t* __restrict__ rgrp,
-                                                  int32_t qg, const float* __restrict__ rq, int32_t n) {
+                                                  int32_t qg, const float* __restrict__ rq) {
   const int lane = threadIdx.x % kWave;
   const int pos = blockIdx.x * (blockDim.x / kWave) + threadIdx.x / kWave;
   if (pos >= B) return;
@@ -988,7 +988,8 @@ __global__ void __launch_bounds__(256) k_finalize(const uint64_t* __restrict__ p
       const uint64_t key = jj < KTOP ? m.v[jj < KTOP ? jj : 0] : 0ull;
       int32_t y = key_index(key);
       float sc = key_score(key);
-      if (rq != nullptr) scale_match(key, m.v[0], rq[pos], n, jj, y, sc);
+      if constexpr (KTOP == 1)
+        if (rq != nullptr) scale_match(key, rq[pos], y, sc);
       idx_out[static_cast<int64_t>(b) * k + jj] = y;
       score_out[static_cast<int64_t>(b) * k + jj] = sc;
     }
@@ -997,17 +998,17 @@ __global__ void __launch_bounds__(256) k_finalize(const uint64_t* __restrict__ p
 
 hipError_t launch_finalize(const uint64_t* partial, const int32_t* perm, int32_t B, int32_t R, int32_t k, int KTOP,
                            int32_t* idx_out, float* score_out, hipStream_t st, const int32_t* rgrp, int32_t qg,
-                           const float* rq, int32_t n) {
+                           const float* rq) {
   const dim3 grid((B + kWaves - 1) / kWaves);
   if (KTOP == 1)
-    hipLaunchKernelGGL(k_finalize<1>, grid, dim3(kThreads), 0, st, partial, perm, B, R, k, idx_out, score_out, rgrp, qg, rq,
-                       n);
+    hipLaunchKernelGGL(k_finalize<1>, grid, dim3(kThreads), 0, st, partial, perm, B, R, k, idx_out, score_out, rgrp, qg,
+                       rq);
   else if (KTOP == 4)
-    hipLaunchKernelGGL(k_finalize<4>, grid, dim3(kThreads), 0, st, partial, perm, B, R, k, idx_out, score_out, rgrp, qg, rq,
-                       n);
+    hipLaunchKernelGGL(k_finalize<4>, grid, dim3(kThreads), 0, st, partial, perm, B, R, k, idx_out, score_out, rgrp, qg,
+                       rq);
   else
-    hipLaunchKernelGGL(k_finalize<8>, grid, dim3(kThreads), 0, st, partial, perm, B, R, k, idx_out, score_out, rgrp, qg, rq,
-                       n);
+    hipLaunchKernelGGL(k_finalize<8>, grid, dim3(kThreads), 0, st, partial, perm, B, R, k, idx_out, score_out, rgrp, qg,
+                       rq);
   return hipGetLastError();
 }
 
