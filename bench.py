@@ -81,19 +81,14 @@ def counter_traffic(workload, kernel):
 
 
 def scan_kernels(s):
-    """The scan kernel the library launches for each half of full-size workload
-    s's batch: the split-k and split-depth scans for a store of a few thousand
-    entries; else the semantic top-1 scan k_sem_mm for k = 1, k_sem_scan for
-    more, the bf16 top-1 trajectory scan k_traj_mm for bf16 stores, k = 1 and
-    more than 128 queries per launch, and k_traj_scan."""
-    small = s.n < 5000
-    sem = None
+    """The scan kernel the library launches for each half of workload s's
+    batch (the library's own choice; without the shape that follows a name)."""
+    import paper_2502_05370_amd as fm
+    sem = traj = None
     if s.B_sem:
-        sem = "k_sem_split" if small else ("k_sem_mm" if s.k == 1 else "k_sem_scan")
-    traj = None
+        sem = fm.debug_scan_name(s.L, s.E, s.n, s.B_sem, s.k, s.map_dtype, d_emb=s.d_emb).split()[0]
     if s.B_traj:
-        wide = s.map_dtype == "bf16" and s.k == 1 and min(s.B_traj, 1024) > 128
-        traj = "k_traj_split" if small else ("k_traj_mm" if wide else "k_traj_scan")
+        traj = fm.debug_scan_name(s.L, s.E, s.n, s.B_traj, s.k, s.map_dtype, max_depth=s.L).split()[0]
     return sem, traj
 
 
