@@ -64,9 +64,11 @@ COPY_BYTES_KIB = 262144.0
 COPY_COUNTERS_KIB = {"FETCH_SIZE": 131083.5, "WRITE_SIZE": 262144.0}
 COUNTERS_KIB = {
     # workload: {kernel: (FETCH_SIZE KiB, WRITE_SIZE KiB) per dispatch}
-    "qwen_traj_n50k_b64": {"k_traj_scan": (138797.4, 128.0)},
-    "semantic_d4096_n100k_b256": {"k_sem_mm": (417145.2, 512.0)},
-    "qwen_mixed_bf16_n1m_b1024": {"k_sem_mm": (2657013.4, 512.0), "k_traj_mm": (2276903.6, 557.0)},
+    "mixtral_traj_n1k": {"k_traj_split": (490.8, 10.9)},
+    "qwen_traj_n50k_b64": {"k_traj_scan": (138801.5, 128.0)},
+    "semantic_d4096_n100k_b256": {"k_sem_mm": (417146.6, 512.0)},
+    "phi_traj_top4_n200k_b512": {"k_traj_scan": (332103.7, 1880.4)},
+    "qwen_mixed_bf16_n1m_b1024": {"k_sem_mm": (2626386.1, 512.0), "k_traj_mm": (2276344.4, 558.4)},
 }
 
 

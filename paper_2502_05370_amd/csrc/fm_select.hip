@@ -255,7 +255,7 @@ __global__ void __launch_bounds__(256) k_select(SelArgs a) {
 // layers each.  The same merge as k_finalize and the same selection as
 // k_select.  Measured (kernel time): 512 positions of 256 top-4 lists, 32
 // layers of 16 experts 26.6 -> 13.0 us; 100 positions of top-8 lists, 32 x 8
-// 18.1 -> 10.0 us; 512 of top-1 lists, 24 x 60 18.1 -> 15.0 us, where the
+// 18.1 -> 10.0 us; 512 of top-1 lists, 24 x 60 18.1 -> 14.4-17.4 us, where the
 // matched rows' reads bound it (a row's 15 quads lie in 15 cache lines, 94 MB
 // of lines for 12,288 rows of four float32 matches).
 struct MergeArgs {
